@@ -133,6 +133,59 @@ constexpr int kk_used(int NT) {
   return NT == 1 ? 4 : NT == 2 ? 7 : NT == 3 ? 9 : NT == 4 ? 16 : NT == 6 ? 21 : NT == 7 ? 25 : NT == 8 ? 31 : NT * 4;
 }
 
+// ---------------------------------------------------------- device helpers
+
+// Workgroups are dispatched to the 8 XCDs of the chip in turn, and each XCD
+// has its own L2.  This maps launch order to work order so that XCD x runs
+// the x-th contiguous eighth of the work items: neighbouring chunks (which
+// share most of their near-field sources) then meet in the same L2.
+__device__ __forceinline__ int xcd_block(int bid, int n) {
+  constexpr int NX = 8;
+  const int q = n / NX, r = n - q * NX;
+  const int x = bid % NX, k = bid / NX;
+  return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
+}
+
+// One batch of up to 64 near leaves of a target leaf, one per lane (entries
+// eb + lane < e1 of the near list), for the part [lo, hi) of the concatenated
+// sources of the list.  `seen` counts the sources of the earlier batches.  A
+// lane receives its leaf and the range of its sources that the part takes
+// (WHOLE: a leaf goes entirely to the part that holds its first source); the
+// result marks the lanes with any.  A leaf's index and range then come from
+// its lane, not from a chain of dependent loads per leaf, which at low
+// occupancy cost a wave more than the leaf's pairs.
+template <bool WHOLE>
+__device__ __forceinline__ unsigned long long near_batch(const int4 *__restrict__ leaf_range,
+                                                         const int32_t *__restrict__ near_idx, int eb, int e1,
+                                                         bool charges, int lo, int hi, int &seen, int &l_sl, int &l_b,
+                                                         int &l_n) {
+  const int lane = threadIdx.x & 63;
+  l_sl = -1;
+  l_b = l_n = 0;
+  if (eb + lane < e1) {
+    l_sl = near_idx[eb + lane];
+    const int4 sr = leaf_range[l_sl];
+    l_b = charges ? sr.z : sr.x;
+    l_n = (charges ? sr.w : sr.y) - l_b;
+  }
+  int inc = l_n;  // inclusive prefix sum over the lanes
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int up = __shfl_up(inc, o);
+    if (lane >= o) inc += up;
+  }
+  const int first = seen + inc - l_n;  // place of the leaf's first source
+  seen += __builtin_amdgcn_readlane(inc, 63);
+  if (WHOLE) {
+    if (first < lo || first >= hi) l_n = 0;
+  } else {
+    const int cb = max(lo - first, 0), ce = min(hi - first, l_n);
+    l_b += cb;
+    l_n = ce - cb;
+  }
+  return __ballot(l_n > 0);
+}
+
 // ---------------------------------------------------------------- tables
 
 // FP64 translation operators for order p and a MAC (host-built, cached).
@@ -263,6 +316,9 @@ struct Tree {
   // P2P work decomposition: (leaf, first sorted index, count, lane groups)
   // per chunk of at most 64 targets of one leaf
   DBuf<int4> chunk_p, chunk_q;
+  DBuf<int2> near_cnt;           // per leaf: panels and charges of its near leaves
+  int near_max = 0;              // longest near list of a leaf
+  int64_t near_pairs[2][2] = {}; // near-field pairs [source: panels, charges][target: panels, charges]
   int64_t nchunk_p = 0, nchunk_q = 0;
 
   PrecBufs *pb32 = nullptr, *pb64 = nullptr;
@@ -319,6 +375,10 @@ void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, hipStream_t 
 void radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, int bits, hipStream_t s);
 
 // fmm.hip
+// parts the near field of a target chunk is split into, one wave each, for
+// products that keep `sums` near sums per target
+int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, bool f64, int sums);
+
 enum SrcKind { SRC_PANEL_MONO = 0, SRC_PANEL_DIP = 1, SRC_PANEL_MONODIP = 2, SRC_CHARGE_MONO = 3 };
 enum TgtKind { TGT_PANEL = 0, TGT_CHARGE = 1 };
 enum OutKind { OUT_POT = 0, OUT_NGRAD = 1, OUT_POTGRAD = 2 };
@@ -340,6 +400,7 @@ struct FmmRequest {
   bool far_only = false;  // skip the near field (the caller adds its own direct sums)
 };
 
+void fmm_init(Tree &T);  // second stream, events and switches of the tree, once
 void fmm_apply(Tree &T, int precision, const FmmRequest &rq, hipStream_t s);
 void fmm_free(Tree &T);
 void debug_expansions(Tree &T, int precision, int which, double *out_host, hipStream_t s);

@@ -44,7 +44,8 @@ struct PrecBufs {
   DBuf<char> E;                 // real [nleaf * 4 * ps]
   DBuf<double> dbg_near, dbg_far;  // sorted-order raw fields (only while debug recording is on)
   bool dbg_valid = false;          // the last product recorded them
-  DBuf<double> near_out;           // near field per target (sorted order)
+  DBuf<double> near_out;           // near field per target (sorted order), per part
+  DBuf<float> leaf_out;            // FP32 near field of several parts: leaf totals per lane
   int last_tgt = 0;
   bool have = false;
 };
@@ -358,17 +359,6 @@ __global__ void k_m2m_sum(int ps, int64_t cp0, int64_t CP, int64_t cl0, const in
 }
 
 // -------------------------------------------------------------------- M2L
-
-// Workgroups are dispatched to the 8 XCDs of the chip in turn, and each XCD
-// has its own L2.  This maps launch order to work order so that XCD x runs
-// the x-th contiguous eighth of the work items: neighbouring chunks (which
-// share most of their near-field sources) then meet in the same L2.
-__device__ __forceinline__ int xcd_block(int bid, int n) {
-  constexpr int NX = 8;
-  const int q = n / NX, r = n - q * NX;
-  const int x = bid % NX, k = bid / NX;
-  return x < r ? x * (q + 1) + k : r * (q + 1) + (x - r) * q + k;
-}
 
 // Offset-grouped dense M2L on MFMA.  A work tile is 4 waves x RT x 16
 // consecutive pairs of one offset group (pairs are sorted by offset, all
@@ -1198,39 +1188,52 @@ __global__ void __launch_bounds__(256) k_downward(int p, int ps, int rs, int com
 // One source-target pair.  Monopole: lp += w/r, (lx,ly,lz) += w d/r^3 (=
 // -grad).  Dipole m: lp += m.d/r^3, (lx,ly,lz) += 3 (m.d) d/r^5 - m/r^3 (=
 // -grad).  d = target - source, ri = 1/r (0 for the excluded self pair).
+// Every fused multiply-add is written out, so that the rounding of a pair does
+// not depend on how the compiler contracts the loop around it: the near field
+// gives the same bits from every path it takes.
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+template <class R>
+__device__ __forceinline__ R dot3(R ax, R ay, R az, R bx, R by, R bz) {
+#pragma clang fp contract(off)
+  return fma_(az, bz, fma_(ax, bx, ay * by));
+}
+
 template <class R, int SRC, int OUT>
 __device__ __forceinline__ void pair_eval(const typename V4<R>::T &s4, const typename V4<R>::T &m4, R dx, R dy, R dz,
                                           R ri, R &lp, R &lx, R &ly, R &lz) {
+#pragma clang fp contract(off)
   if (SRC == SRC_PANEL_MONO || SRC == SRC_CHARGE_MONO) {
-    const R wr = s4.w * ri;
-    if (OUT == OUT_POT || OUT == OUT_POTGRAD) lp += wr;
-    if (OUT != OUT_POT) {
-      const R t = wr * ri * ri;
-      lx += t * dx;
-      ly += t * dy;
-      lz += t * dz;
+    static_assert(SRC == SRC_PANEL_DIP || SRC == SRC_PANEL_MONODIP || OUT != OUT_POTGRAD, "not a product");
+    if (OUT == OUT_POT) {
+      lp = fma_(s4.w, ri, lp);
+    } else {
+      const R t = s4.w * ri * ri * ri;
+      lx = fma_(t, dx, lx);
+      ly = fma_(t, dy, ly);
+      lz = fma_(t, dz, lz);
     }
   } else {
     const R ri2 = ri * ri;
     const R ri3 = ri2 * ri;
-    const R md = m4.x * dx + m4.y * dy + m4.z * dz;
-    R t = R(0), pot = md * ri3;
-    if (SRC == SRC_PANEL_MONODIP) {
+    const R md = dot3<R>(m4.x, m4.y, m4.z, dx, dy, dz);
+    if (OUT == OUT_POT) {
+      if (SRC == SRC_PANEL_MONODIP)
+        lp += fma_(s4.w, ri, md * ri3);
+      else
+        lp = fma_(md, ri3, lp);
+    } else {
+      static_assert(SRC != SRC_PANEL_DIP || OUT == OUT_POT, "not a product");
       const R wr = s4.w * ri;
-      pot += wr;
-      t = wr * ri2;
-    }
-    if (OUT == OUT_POT || OUT == OUT_POTGRAD) lp += pot;
-    if (OUT != OUT_POT) {
-      t += R(3) * md * ri3 * ri2;
-      lx += t * dx - m4.x * ri3;
-      ly += t * dy - m4.y * ri3;
-      lz += t * dz - m4.z * ri3;
+      lp += fma_(md, ri3, wr);
+      const R t = fma_(wr, ri2, R(3) * md * ri3 * ri2);
+      lx += fma_(t, dx, -(m4.x * ri3));
+      ly += fma_(t, dy, -(m4.y * ri3));
+      lz += fma_(t, dz, -(m4.z * ri3));
     }
   }
 }
-
-
 
 // 1/r^3 in FP64 from r^2 without forming 1/r: with y0 the hardware estimate
 // of r^-1/2 and e = 1 - r^2 y0^2, the Newton-corrected 1/r^3 is
@@ -1254,12 +1257,12 @@ __device__ __forceinline__ void pair_eval_r2(const typename V4<R>::T &s4, const 
   constexpr bool F64 = std::is_same<R, double>::value;
   if constexpr (F64 && (SRC == SRC_PANEL_MONO || SRC == SRC_CHARGE_MONO) && OUT == OUT_NGRAD) {
     const double t = skip ? 0.0 : s4.w * inv_r3(r2);
-    lx += t * dx;
-    ly += t * dy;
-    lz += t * dz;
+    lx = fma_(t, dx, lx);
+    ly = fma_(t, dy, ly);
+    lz = fma_(t, dz, lz);
   } else if constexpr (F64 && SRC == SRC_PANEL_DIP && OUT == OUT_POT) {
     const double ri3 = skip ? 0.0 : inv_r3(r2);
-    lp += (m4.x * dx + m4.y * dy + m4.z * dz) * ri3;
+    lp = fma_(dot3<R>(m4.x, m4.y, m4.z, dx, dy, dz), ri3, lp);
   } else {
     const R ri = skip ? R(0) : rsq(r2);
     pair_eval<R, SRC, OUT>(s4, m4, dx, dy, dz, ri, lp, lx, ly, lz);
@@ -1310,7 +1313,13 @@ struct P2PArgs {
   int accumulate;
   double *y;
   double *dbg_near, *dbg_far;  // sorted order, may be NULL
-  double *near_out;            // near field per target, sorted order ([n] or [4n])
+  double *near_out;            // near field per target, sorted order ([n] or [4n]) per part
+  const int2 *near_cnt;        // sources of each leaf's near leaves (panels, charges)
+  int nseg;                    // parts of the near field
+  int nsum;                    // parts that the combine adds
+  size_t seg_stride;           // reals of near_out per part
+  float *leaf_out;             // FP32, several parts: leaf totals [chunk][near_max][components][64 lanes]
+  int near_max;                // longest near list
 };
 
 // Near field (P2P).  One wave per chunk of up to 64 targets of one leaf.  A
@@ -1357,7 +1366,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
     int sxi, syi, szi;
     xyz_of(a.leaf_xyz[sl], sxi, syi, szi);
     // target relative to the source leaf centre
-    const R ux = tx + R(txi - sxi) * sL, uy = ty + R(tyi - syi) * sL, uz = tz + R(tzi - szi) * sL;
+    const R ux = fma_(R(txi - sxi), sL, tx), uy = fma_(R(tyi - syi), sL, ty), uz = fma_(R(tzi - szi), sL, tz);
     R lp = R(0), lx = R(0), ly = R(0), lz = R(0);
     const bool self = (SRC != SRC_CHARGE_MONO) && (TGT == TGT_PANEL) && (sl == leaf);
     if (G == 1) {
@@ -1367,7 +1376,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
         for (int j = sb; j < se; ++j) {
           const R4 s4 = spos[j];
           const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
-          const R r2 = dx * dx + dy * dy + dz * dz;
+          const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
           // K'_ii = 0: the self panel is skipped by index
           pair_accumulate<R, SRC, OUT>(s4, sdip, j, dx, dy, dz, r2, j == ti, lp, lx, ly, lz);
         }
@@ -1375,8 +1384,8 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
         // software pipelined: the records of the next PF sources are
         // requested before the current PF are evaluated, so the wait for
         // the scalar loads falls after the arithmetic
-        constexpr int PF = 4;
         constexpr bool DIPS = SRC == SRC_PANEL_DIP || SRC == SRC_PANEL_MONODIP;
+        constexpr int PF = sizeof(R) == 8 && DIPS ? 2 : 4;  // 2 PF records in scalar registers
         int j = sb;
         if (se - sb >= 2 * PF) {
           R4 cs[PF], cm[PF];
@@ -1395,7 +1404,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
 #pragma unroll
             for (int u = 0; u < PF; ++u) {
               const R dx = ux - cs[u].x, dy = uy - cs[u].y, dz = uz - cs[u].z;
-              const R r2 = dx * dx + dy * dy + dz * dz;
+              const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
               pair_eval_r2<R, SRC, OUT>(cs[u], cm[u], dx, dy, dz, r2, false, lp, lx, ly, lz);
             }
 #pragma unroll
@@ -1407,7 +1416,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
 #pragma unroll
           for (int u = 0; u < PF; ++u) {
             const R dx = ux - cs[u].x, dy = uy - cs[u].y, dz = uz - cs[u].z;
-            const R r2 = dx * dx + dy * dy + dz * dz;
+            const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
             pair_eval_r2<R, SRC, OUT>(cs[u], cm[u], dx, dy, dz, r2, false, lp, lx, ly, lz);
           }
           j += PF;
@@ -1415,7 +1424,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
         for (; j < se; ++j) {
           const R4 s4 = spos[j];
           const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
-          const R r2 = dx * dx + dy * dy + dz * dz;
+          const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
           pair_accumulate<R, SRC, OUT>(s4, sdip, j, dx, dy, dz, r2, false, lp, lx, ly, lz);
         }
       }
@@ -1437,7 +1446,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
           for (int jj = g; jj < cnt; jj += G) {
             const R4 s4 = src_s[jj];
             const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
-            const R r2 = dx * dx + dy * dy + dz * dz;
+            const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
             pair_eval_r2<R, SRC, OUT>(s4, DIPS ? dip_s[jj] : s4, dx, dy, dz, r2, base + jj == ti, lp, lx, ly, lz);
           }
         } else {
@@ -1445,7 +1454,7 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
           for (int jj = g; jj < cnt; jj += G) {
             const R4 s4 = src_s[jj];
             const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
-            const R r2 = dx * dx + dy * dy + dz * dz;
+            const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
             pair_eval_r2<R, SRC, OUT>(s4, DIPS ? dip_s[jj] : s4, dx, dy, dz, r2, false, lp, lx, ly, lz);
           }
         }
@@ -1499,6 +1508,281 @@ __global__ void __launch_bounds__(64) k_p2p_near(P2PArgs a) {
   }
 }
 
+// A value at an index that is uniform over the wave, through the scalar
+// cache: the constant address space says that no store of the kernel writes
+// it.
+template <class T4>
+__device__ __forceinline__ T4 uniform_load(const T4 *p) {
+  typedef decltype(T4::x) Vec __attribute__((ext_vector_type(4)));
+  const Vec v = *(const __attribute__((address_space(4))) Vec *)(p);
+  T4 r;
+  r.x = v.x;
+  r.y = v.y;
+  r.z = v.z;
+  r.w = v.w;
+  return r;
+}
+
+// The near field in parts: one wave per task, a chunk against one of `nseg`
+// parts of the sources of its near leaves, counted in list order.  Lanes,
+// lane groups and the sum over a leaf are those of k_p2p_near.  In FP64 the
+// parts are equal, and the combine adds their results (near_out[part]) in
+// order.  In FP32 they are whole leaves, and the leaf totals of every lane go
+// to leaf_out; k_near_sum takes them through the compensated sum of k_p2p_near
+// in its order, so that the bits do not depend on the split.
+// These waves are few, and wait for their loads: the near list is read 64
+// leaves at a time (near_batch), and PF records are requested before the PF at
+// hand are evaluated.  With every SIMD full k_p2p_near's loop, whose wait the
+// other waves cover, is the faster (FP32 A, 10.5 million panels, near field in
+// line: 39.5 against 41.8 ms per product).
+template <class R, int OUT>
+struct NearAcc {
+  // compensated sums of the potential and of the three gradient components
+  R s[4] = {R(0), R(0), R(0), R(0)}, c[4] = {R(0), R(0), R(0), R(0)};
+  __device__ __forceinline__ void add(R lp, R lx, R ly, R lz) {
+    const R v[4] = {lp, lx, ly, lz};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if ((k == 0 && OUT == OUT_NGRAD) || (k > 0 && OUT == OUT_POT)) continue;
+      const R y = v[k] - c[k], t = s[k] + y;
+      c[k] = (t - s[k]) - y;
+      s[k] = t;
+    }
+  }
+  // adds the G lane groups in group order and stores the target's result
+  __device__ __forceinline__ void finish(R (*red)[64], int G, int count, int g, int tl, int ti, const void *tgt_nrm,
+                                         double *near_out) {
+    if (G > 1) {
+      __syncthreads();  // the last staged records are no longer read
+#pragma unroll
+      for (int k = 0; k < 4; ++k) red[k][threadIdx.x] = s[k];
+      __syncthreads();
+      if (g == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          s[k] = red[k][tl];
+          c[k] = R(0);
+        }
+        for (int h = 1; h < G; ++h) {
+          const int o = h * count + tl;
+          add(red[0][o], red[1][o], red[2][o], red[3][o]);
+        }
+      }
+    }
+    if (g != 0) return;
+    if (OUT == OUT_POT) {
+      near_out[ti] = (double)s[0];
+    } else if (OUT == OUT_NGRAD) {
+      const typename V4<R>::T nn = reinterpret_cast<const typename V4<R>::T *>(tgt_nrm)[ti];
+      near_out[ti] = -((double)nn.x * s[1] + (double)nn.y * s[2] + (double)nn.z * s[3]);
+    } else {
+      near_out[4 * (size_t)ti] = (double)s[0];
+      near_out[4 * (size_t)ti + 1] = -(double)s[1];
+      near_out[4 * (size_t)ti + 2] = -(double)s[2];
+      near_out[4 * (size_t)ti + 3] = -(double)s[3];
+    }
+  }
+};
+
+constexpr int near_ncomp(int out) { return out == OUT_POT ? 1 : out == OUT_NGRAD ? 3 : 4; }
+
+template <class R, int SRC, int TGT, int OUT>
+__global__ void __launch_bounds__(64) k_p2p_parts(P2PArgs a) {
+  using R4 = typename V4<R>::T;
+  constexpr bool DIPS = SRC == SRC_PANEL_DIP || SRC == SRC_PANEL_MONODIP;
+  constexpr bool F32 = std::is_same<R, float>::value;
+  constexpr int PF = (!F32 && DIPS) ? 2 : 4;  // records in flight: 2 PF in scalar registers
+  // staged source records during the sweep, group partials after it (the
+  // two never live at once: 64 real4 = 4 x 64 reals)
+  __shared__ R4 src_s[64];
+  __shared__ R4 dip_s[DIPS ? 64 : 1];
+  const int task = xcd_block(blockIdx.x, gridDim.x);
+  const int nseg = a.nseg;
+  const int ci = task / nseg, seg = task - ci * nseg;
+  // (leaf, first target, count, groups); chunks are in Morton order
+  const int4 ch = a.chunks[ci];
+  const int leaf = ch.x, count = ch.z, G = ch.w;
+  const int lane = threadIdx.x;
+  const int g = lane / count, tl = lane - g * count;
+  const bool active = g < G;
+  const int ti = ch.y + tl;
+  const R4 *tpos = reinterpret_cast<const R4 *>(a.tgt_pos);
+  const R4 *spos = reinterpret_cast<const R4 *>(a.src_pos);
+  const R4 *sdip = reinterpret_cast<const R4 *>(a.src_dip);
+  const R4 tp = tpos[ti];
+  const R tx = tp.x, ty = tp.y, tz = tp.z;
+  // ---- near field: direct sum over the near leaves, compensated per leaf
+  NearAcc<R, OUT> acc;
+  int txi, tyi, tzi;
+  xyz_of(a.leaf_xyz[leaf], txi, tyi, tzi);
+  const R sL = (R)a.sL;
+  const int e0 = a.near_ptr[leaf], e1 = a.near_ptr[leaf + 1];
+  // adds the pairs with sources [sb, se) of leaf sl to (lp, lx, ly, lz)
+  auto leaf_pairs = [&](int sl, int sb, int se, int sxyz, R &lp, R &lx, R &ly, R &lz) {
+    int sxi, syi, szi;
+    xyz_of(sxyz, sxi, syi, szi);
+    // target relative to the source leaf centre
+    const R ux = fma_(R(txi - sxi), sL, tx), uy = fma_(R(tyi - syi), sL, ty), uz = fma_(R(tzi - szi), sL, tz);
+    const bool self = (SRC != SRC_CHARGE_MONO) && (TGT == TGT_PANEL) && (sl == leaf);
+    if (G == 1) {
+      // one lane group: the source index is uniform across the wave
+      auto eval = [&](const R4 &s4, const R4 &m4, bool skip) {
+        const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
+        const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
+        pair_eval_r2<R, SRC, OUT>(s4, m4, dx, dy, dz, r2, skip, lp, lx, ly, lz);
+      };
+      if (self) {
+        // K'_ii = 0: the self panel is skipped by index
+        for (int j = sb; j < se; ++j) eval(uniform_load(spos + j), DIPS ? uniform_load(sdip + j) : R4{}, j == ti);
+      } else {
+        auto request = [&](int j, R4(&s4)[PF], R4(&m4)[PF]) {
+#pragma unroll
+          for (int u = 0; u < PF; ++u) {
+            s4[u] = uniform_load(spos + j + u);
+            if (DIPS) m4[u] = uniform_load(sdip + j + u);
+          }
+          __builtin_amdgcn_sched_barrier(0);  // requested before what follows
+        };
+        // scalar loads return in any order, so a wait for one is a wait for
+        // all: the records at hand are waited for before the next are requested
+        auto arrived = [&](const R4(&s4)[PF], const R4(&m4)[PF]) {
+          __asm__ volatile("" ::"s"(s4[0].x));
+          if (DIPS) __asm__ volatile("" ::"s"(m4[0].x));
+        };
+        auto eval_all = [&](const R4(&s4)[PF], const R4(&m4)[PF]) {
+#pragma unroll
+          for (int u = 0; u < PF; ++u) eval(s4[u], m4[u], false);
+        };
+        auto eval_some = [&](const R4(&s4)[PF], const R4(&m4)[PF], int n) {
+#pragma unroll
+          for (int u = 0; u < PF - 1; ++u)
+            if (u < n) eval(s4[u], m4[u], false);
+        };
+        // two sets of PF records in turn; past the end of the leaf they are
+        // the next leaf's (the arrays are padded) and are not used
+        R4 as[PF], am[PF], bs[PF], bm[PF];
+        const int full = (se - sb) / PF, rest = (se - sb) % PF;
+        int j = sb, q = 0;
+        request(j, as, am);
+        for (; q + 2 <= full; q += 2, j += 2 * PF) {
+          arrived(as, am);
+          request(j + PF, bs, bm);
+          eval_all(as, am);
+          arrived(bs, bm);
+          request(j + 2 * PF, as, am);
+          eval_all(bs, bm);
+        }
+        if (q < full) {
+          arrived(as, am);
+          request(j + PF, bs, bm);
+          eval_all(as, am);
+          eval_some(bs, bm, rest);
+        } else {
+          eval_some(as, am, rest);
+        }
+      }
+    } else {
+      // several lane groups: the source leaf is staged in LDS, 64 records at
+      // a time, with one coalesced load; every lane group then reads its own
+      // sources there (a group's lanes read the same record: a broadcast)
+      for (int base = sb; base < se; base += 64) {
+        const int cnt = min(64, se - base);
+        __syncthreads();  // the previous records are no longer read
+        if (lane < cnt) {
+          src_s[lane] = spos[base + lane];
+          if (DIPS) dip_s[lane] = sdip[base + lane];
+        }
+        __syncthreads();
+        if (!active) continue;
+        if (self) {
+          for (int jj = g; jj < cnt; jj += G) {
+            const R4 s4 = src_s[jj];
+            const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
+            const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
+            pair_eval_r2<R, SRC, OUT>(s4, DIPS ? dip_s[jj] : s4, dx, dy, dz, r2, base + jj == ti, lp, lx, ly, lz);
+          }
+        } else {
+#pragma unroll 4
+          for (int jj = g; jj < cnt; jj += G) {
+            const R4 s4 = src_s[jj];
+            const R dx = ux - s4.x, dy = uy - s4.y, dz = uz - s4.z;
+            const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
+            pair_eval_r2<R, SRC, OUT>(s4, DIPS ? dip_s[jj] : s4, dx, dy, dz, r2, false, lp, lx, ly, lz);
+          }
+        }
+      }
+    }
+  };
+  // this part's sources: places [lo, hi) of the concatenated near leaves
+  const int2 tot2 = a.near_cnt[leaf];
+  const int64_t total = (SRC == SRC_CHARGE_MONO) ? tot2.y : tot2.x;
+  const int lo = (int)(total * seg / nseg), hi = (int)(total * (seg + 1) / nseg);
+  int seen = 0;
+  for (int eb = e0; eb < e1 && seen < hi; eb += 64) {
+    int l_sl, l_b, l_n;
+    unsigned long long todo =
+        near_batch<F32>(a.leaf_range, a.near_idx, eb, e1, SRC == SRC_CHARGE_MONO, lo, hi, seen, l_sl, l_b, l_n);
+    const int l_xyz = eb + lane < e1 ? a.leaf_xyz[l_sl] : 0;
+    while (todo) {
+      const int k = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int sb = __builtin_amdgcn_readlane(l_b, k), se = sb + __builtin_amdgcn_readlane(l_n, k);
+      R lp = R(0), lx = R(0), ly = R(0), lz = R(0);
+      leaf_pairs(__builtin_amdgcn_readlane(l_sl, k), sb, se, __builtin_amdgcn_readlane(l_xyz, k), lp, lx, ly, lz);
+      if constexpr (F32) {
+        constexpr int NC = near_ncomp(OUT);
+        float *o = a.leaf_out + ((size_t)ci * a.near_max + (eb + k - e0)) * (NC * 64) + lane;
+        const R v[4] = {lp, lx, ly, lz};
+#pragma unroll
+        for (int c = 0; c < NC; ++c) o[c * 64] = (float)v[OUT == OUT_NGRAD ? c + 1 : c];
+      } else {
+        acc.add(lp, lx, ly, lz);
+      }
+    }
+  }
+  if constexpr (F32) return;
+  acc.finish(reinterpret_cast<R(*)[64]>(src_s), G, count, g, tl, ti, a.tgt_nrm,
+             a.near_out + (size_t)seg * a.seg_stride);
+}
+
+// FP32 near field of several parts: one wave per chunk takes the leaf totals
+// of its lanes, in list order, through the compensated sum of k_p2p_near.
+// Empty leaves have no total.  Bound by the latency of its loads, which are
+// issued 8 leaves at a time.
+template <int SRC, int OUT>
+__global__ void __launch_bounds__(64) k_near_sum(P2PArgs a) {
+  constexpr int NC = near_ncomp(OUT), U = 8;
+  __shared__ float red[4][64];
+  const int ci = blockIdx.x;
+  const int4 ch = a.chunks[ci];
+  const int leaf = ch.x, count = ch.z, G = ch.w;
+  const int lane = threadIdx.x;
+  const int g = lane / count, tl = lane - g * count;
+  NearAcc<float, OUT> acc;
+  const int e0 = a.near_ptr[leaf], ne = a.near_ptr[leaf + 1] - e0;
+  const float *tot = a.leaf_out + (size_t)ci * a.near_max * (NC * 64) + lane;
+  for (int eb = 0; eb < ne; eb += 64) {
+    bool any = false;
+    if (eb + lane < ne) {
+      const int4 sr = a.leaf_range[a.near_idx[e0 + eb + lane]];
+      any = (SRC == SRC_CHARGE_MONO) ? sr.w > sr.z : sr.y > sr.x;
+    }
+    const unsigned long long full = __ballot(any);
+    for (int i = 0; i < min(64, ne - eb); i += U) {
+      float v[U][4];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          v[u][OUT == OUT_NGRAD ? c + 1 : c] = tot[((size_t)min(eb + i + u, ne - 1) * NC + c) * 64];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (full >> (i + u) & 1) acc.add(v[u][0], v[u][1], v[u][2], v[u][3]);
+    }
+  }
+  acc.finish(red, G, count, g, tl, ch.y + tl, a.tgt_nrm, a.near_out);
+}
+
 // Far field (L2P from the leaf's evaluation coefficients, read through the
 // scalar cache) plus the near field, combined into the operator's output in
 // the caller's order: y = alpha x + beta (area) field.
@@ -1545,24 +1829,30 @@ __global__ void __launch_bounds__(64) k_l2p_combine(P2PArgs a) {
   const int64_t u = a.tperm[ti];
   double res[4], near_v, far_v;
   int nres = 1;
-  // near_out is NULL for a far-field-only product
-  const double *no = a.near_out;
+  // the near field's parts in order (near_out is NULL for a far-field-only product)
+  constexpr int NC = OUT == OUT_POTGRAD ? 4 : 1;
+  double nv[NC] = {};
+  if (a.near_out) {
+    const double *no = a.near_out + NC * (size_t)ti;
+#pragma unroll 8
+    for (int q = 0; q < a.nsum; ++q, no += a.seg_stride)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) nv[k] += no[k];
+  }
+  near_v = nv[0];
   if (OUT == OUT_POT) {
-    near_v = no ? no[ti] : 0.0;
     far_v = (double)fp;
     res[0] = near_v + far_v;
   } else if (OUT == OUT_NGRAD) {
     const R4 nn = reinterpret_cast<const R4 *>(a.tgt_nrm)[ti];
-    near_v = no ? no[ti] : 0.0;
     far_v = (double)nn.x * fgx + (double)nn.y * fgy + (double)nn.z * fgz;
     res[0] = near_v + far_v;
   } else {
-    near_v = no ? no[4 * (size_t)ti] : 0.0;
     far_v = (double)fp;
     res[0] = near_v + far_v;
-    res[1] = (no ? no[4 * (size_t)ti + 1] : 0.0) + (double)fgx;
-    res[2] = (no ? no[4 * (size_t)ti + 2] : 0.0) + (double)fgy;
-    res[3] = (no ? no[4 * (size_t)ti + 3] : 0.0) + (double)fgz;
+    res[1] = nv[NC > 1 ? 1 : 0] + (double)fgx;
+    res[2] = nv[NC > 2 ? 2 : 0] + (double)fgy;
+    res[3] = nv[NC > 3 ? 3 : 0] + (double)fgz;
     nres = 4;
   }
   if (a.dbg_near) {
@@ -1655,8 +1945,9 @@ static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
     pb = new PrecBufs();
     const size_t rs = (prec == BEMFMM_FP64) ? 8 : 4;
     const int64_t npts = std::max<int64_t>(std::max(T.N, T.Q), 1);
-    pb->src_pos.alloc(npts * 4 * rs);
-    pb->src_dip.alloc(npts * 4 * rs);
+    // the near field reads up to 8 records past a leaf's sources
+    pb->src_pos.alloc((npts + 8) * 4 * rs);
+    pb->src_dip.alloc((npts + 8) * 4 * rs);
     pb->M.alloc((size_t)T.ncell_tot * T.ps * rs);
     pb->L.alloc((size_t)T.ncell_tot * T.ps * rs);
     pb->m2l_out.alloc((size_t)std::max<int64_t>(T.nfar, 1) * T.ps * rs);
@@ -1670,6 +1961,36 @@ static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
     pb->prec = prec;
   }
   return *pb;
+}
+
+// Parts the near field of a target chunk is split into.  A wave alone on its
+// SIMD takes about 150 clocks per source (64 pairs), eight waves together
+// about 43, and waves of unequal length leave SIMDs idle at the end.  Chunks
+// are therefore split until there are 8 waves per SIMD, but never below 64
+// sources per part, about one leaf, which covers a wave's fixed cost, nor
+// into more than 32 parts, whose sum the combine takes per target.
+// Measured on an MI355X, whole chunks -> this rule: FP64 solve, 1,280 panels
+// (24 chunks) 1319 -> 862 us; FP64 A^T, 327,680 panels (7,415 chunks) 2.10 ->
+// 1.82 ms; FP32 A, 5,120 panels 203 -> 72 us, 20,480 panels (452 chunks) 254 ->
+// 153 us.
+// One sum per target (the potential) gains throughout: FP32 A^T at 128,000
+// panels 603 -> 533 us, at 327,680 981 -> 917 us.  With the three of a
+// gradient, parts stop where they cost more than they give.  FP32 parts store
+// them per target and near leaf: at more than one chunk per SIMD that pays for
+// long lists only (FP32 A, 62,720 and 184,320 panels, 2,100 and 1,400 sources per
+// target: 264 -> 290 and 541 -> 612 us; 128,000 panels, 4,400 sources: 584 -> 508
+// us).  In FP64 it is the waves beside the M2L that cost: at 4 chunks per SIMD
+// and below parts gain (FP64 A, 81,920 and 128,000 panels: 637 -> 571 and 1099 ->
+// 857 us), above they lose (184,320 and 327,680: 1248 -> 1287 and 1846 -> 1887 us).
+int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, bool f64, int sums) {
+  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32, LONG_LIST = 3500;
+  if (nchunks <= 0) return 1;
+  const int64_t simds = 4 * (int64_t)T.n_cu;
+  const int64_t npts = std::max<int64_t>(tgt_charges ? T.Q : T.N, 1);
+  const int64_t mean = T.near_pairs[src_charges][tgt_charges] / npts;  // sources per target
+  if (sums > 1 && (f64 ? nchunks > 4 * simds : nchunks > simds && mean < LONG_LIST)) return 1;
+  const int64_t want = cdiv(WAVES_PER_SIMD * simds, nchunks);
+  return (int)std::max<int64_t>(1, std::min(std::min(want, mean / MIN_SOURCES), MAX_PARTS));
 }
 
 template <class R>
@@ -1823,6 +2144,15 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   a.dbg_near = T.debug_record ? B.dbg_near.p : nullptr;
   a.dbg_far = T.debug_record ? B.dbg_far.p : nullptr;
   B.dbg_valid = T.debug_record;
+  a.near_cnt = T.near_cnt.p;
+  a.nseg = rq.far_only ? 1 : near_parts(T, src_charges, tgt_ch, nchunks, f64, near_ncomp(rq.out));
+  a.nsum = f64 ? a.nseg : 1;
+  const int64_t ntgt = tgt_ch ? T.Q : T.N;
+  a.seg_stride = (size_t)ntgt * (rq.out == OUT_POTGRAD ? 4 : 1);
+  if (!rq.far_only) B.near_out.reserve(a.nsum * a.seg_stride);
+  a.near_max = T.near_max;
+  if (!f64 && a.nseg > 1) B.leaf_out.reserve((size_t)nchunks * T.near_max * near_ncomp(rq.out) * 64);
+  a.leaf_out = B.leaf_out.p;
   a.near_out = rq.far_only ? nullptr : B.near_out.p;
   B.last_tgt = rq.tgt;
   // The near field runs on the second stream, forked from the caller's
@@ -1857,9 +2187,17 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
     if (nchunks > 0) {
       HIP_OK(hipStreamWaitEvent(ss, T.ev_fork, 0));
       const P2PArgs &ap = a;
-      const unsigned nb = (unsigned)nchunks;
+      const unsigned nb = (unsigned)(nchunks * a.nseg);
       prof_begin(T, ST_P2P, ss);
-#define P2P_CALL(S, Tg, O) k_p2p_near<R, S, Tg, O><<<nb, 64, 0, ss>>>(ap)
+#define P2P_CALL(S, Tg, O)                                                                    \
+  do {                                                                                        \
+    if (a.nseg == 1) {                                                                        \
+      k_p2p_near<R, S, Tg, O><<<nb, 64, 0, ss>>>(ap);                                         \
+    } else {                                                                                  \
+      k_p2p_parts<R, S, Tg, O><<<nb, 64, 0, ss>>>(ap);                                        \
+      if (!f64) k_near_sum<S, O><<<(unsigned)nchunks, 64, 0, ss>>>(ap);                       \
+    }                                                                                         \
+  } while (0)
       if (!tgt_ch) {
         if (rq.src == SRC_PANEL_MONO && rq.out == OUT_NGRAD) P2P_CALL(SRC_PANEL_MONO, TGT_PANEL, OUT_NGRAD);
         else if (rq.src == SRC_PANEL_DIP && rq.out == OUT_POT) P2P_CALL(SRC_PANEL_DIP, TGT_PANEL, OUT_POT);
@@ -2006,27 +2344,31 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   prof_collect(T);
 }
 
+// The tree's second stream, events and switches, at its first product.
+void fmm_init(Tree &T) {
+  if (T.ev_init) return;
+  for (auto &e : T.ev) HIP_OK(hipEventCreate(&e));
+  HIP_OK(hipEventCreateWithFlags(&T.ev_fork, hipEventDisableTiming));
+  HIP_OK(hipEventCreateWithFlags(&T.ev_join, hipEventDisableTiming));
+  HIP_OK(hipStreamCreateWithFlags(&T.side_stream, hipStreamNonBlocking));  // default priority
+  T.ev_init = true;
+  if (const char *e = getenv("BEMFMM_CONCURRENT_P2P")) T.concurrent = atoi(e) != 0;
+  if (const char *e = getenv("BEMFMM_M2L_PERSISTENT")) T.m2l_persistent = atoi(e) != 0;
+  if (const char *e = getenv("BEMFMM_M2L_SPLIT")) T.m2l_split = atoi(e) != 0;
+  // the split-bf16 M2L takes more dynamic LDS than the default limit
+  HIP_OK(hipFuncSetAttribute((const void *)k_m2l_bf<NT_FIXED, RB_FIXED>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                             M2L_BF_LDS));
+  if (const char *e = getenv("BEMFMM_FORK_AT")) T.fork_at = std::min(std::max(atoi(e), -1), (int)FORK_AFTER_M2L);
+  int dev = 0;
+  HIP_OK(hipGetDevice(&dev));
+  HIP_OK(hipDeviceGetAttribute(&T.n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+}
+
 void fmm_apply(Tree &T, int precision, const FmmRequest &rq, hipStream_t s) {
   const int prec = (precision == BEMFMM_FP64) ? BEMFMM_FP64 : BEMFMM_FP32;
   if (rq.tgt == TGT_CHARGE && T.Q == 0) return;
+  fmm_init(T);
   PrecBufs &B = bufs(T, prec, s);
-  if (!T.ev_init) {
-    for (auto &e : T.ev) HIP_OK(hipEventCreate(&e));
-    HIP_OK(hipEventCreateWithFlags(&T.ev_fork, hipEventDisableTiming));
-    HIP_OK(hipEventCreateWithFlags(&T.ev_join, hipEventDisableTiming));
-    HIP_OK(hipStreamCreateWithFlags(&T.side_stream, hipStreamNonBlocking));  // default priority
-    T.ev_init = true;
-    if (const char *e = getenv("BEMFMM_CONCURRENT_P2P")) T.concurrent = atoi(e) != 0;
-    if (const char *e = getenv("BEMFMM_M2L_PERSISTENT")) T.m2l_persistent = atoi(e) != 0;
-    if (const char *e = getenv("BEMFMM_M2L_SPLIT")) T.m2l_split = atoi(e) != 0;
-    // the split-bf16 M2L takes more dynamic LDS than the default limit
-    HIP_OK(hipFuncSetAttribute((const void *)k_m2l_bf<NT_FIXED, RB_FIXED>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               M2L_BF_LDS));
-    if (const char *e = getenv("BEMFMM_FORK_AT")) T.fork_at = std::min(std::max(atoi(e), -1), (int)FORK_AFTER_M2L);
-    int dev = 0;
-    HIP_OK(hipGetDevice(&dev));
-    HIP_OK(hipDeviceGetAttribute(&T.n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  }
   T.prof_kind = (rq.op >= 0 && rq.op < 6) ? rq.op : 6;
   T.prof_prec = prec == BEMFMM_FP64 ? 0 : 1;
   T.prof_now = T.prof && (T.prof_op < 0 || T.prof_op == rq.op) && (T.prof_sel_prec < 0 || T.prof_sel_prec == T.prof_prec);

@@ -701,19 +701,47 @@ __global__ void k_gather_charges(const int32_t *__restrict__ perm, const int32_t
   q32[i] = make_float4((float)rx, (float)ry, (float)rz, 0.0f);
 }
 
-__global__ void k_p2p_pairs(const int4 *__restrict__ range, int64_t C, const int32_t *__restrict__ near_ptr,
-                            const int32_t *__restrict__ near_idx, unsigned long long *__restrict__ out) {
-  int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  unsigned long long s = 0;
+// Per leaf, one wave: the panels and charges of its near leaves, the
+// near-field pairs they make with its own (out[2 * source kind + target
+// kind]) and the longest near list (out[4]).
+__global__ void __launch_bounds__(256) k_near_counts(const int4 *__restrict__ range, int64_t C,
+                                                     const int32_t *__restrict__ near_ptr,
+                                                     const int32_t *__restrict__ near_idx, int2 *__restrict__ cnt,
+                                                     unsigned long long *__restrict__ out) {
+  __shared__ unsigned long long sh[4][4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t t = (int64_t)blockIdx.x * 4 + wave;
+  int np = 0, nq = 0;
   if (t < C) {
-    int4 rt = range[t];
-    unsigned long long nt = (unsigned long long)(rt.y - rt.x);
-    for (int e = near_ptr[t]; e < near_ptr[t + 1]; ++e) {
-      int4 rs = range[near_idx[e]];
-      s += nt * (unsigned long long)(rs.y - rs.x);
+    for (int e = near_ptr[t] + lane; e < near_ptr[t + 1]; e += 64) {
+      const int4 r = range[near_idx[e]];
+      np += r.y - r.x;
+      nq += r.w - r.z;
     }
   }
-  if (s) atomicAdd(out, s);
+  for (int o = 32; o > 0; o >>= 1) {
+    np += __shfl_xor(np, o);
+    nq += __shfl_xor(nq, o);
+  }
+  if (lane == 0) {
+    unsigned long long tp = 0, tq = 0;
+    if (t < C) {
+      cnt[t] = make_int2(np, nq);
+      atomicMax(out + 4, (unsigned long long)(near_ptr[t + 1] - near_ptr[t]));
+      const int4 r = range[t];
+      tp = (unsigned long long)(r.y - r.x);
+      tq = (unsigned long long)(r.w - r.z);
+    }
+    sh[wave][0] = np * tp;
+    sh[wave][1] = np * tq;
+    sh[wave][2] = nq * tp;
+    sh[wave][3] = nq * tq;
+  }
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const unsigned long long v = sh[0][threadIdx.x] + sh[1][threadIdx.x] + sh[2][threadIdx.x] + sh[3][threadIdx.x];
+    if (v) atomicAdd(out + threadIdx.x, v);
+  }
 }
 
 template <class T>
@@ -1354,18 +1382,21 @@ void build_tree(Tree &T, const double *verts, int64_t nv, const int32_t *tris, i
     LAUNCH_OK();
     if (read_err(err, s) & 16) BF_THROW(BEMFMM_EDEVICE, "tree build: a charge lies outside its leaf cell");
   }
-  // work estimate: P2P panel pairs
+  // near-field work: sources per leaf and pairs per kind
   {
     DBuf<unsigned long long> acc;
-    acc.alloc(1);
+    acc.alloc(5);
     acc.zero(s);
-    k_p2p_pairs<<<cdiv(CL, TB), TB, 0, s>>>(T.crange.p + T.coff[L], CL, T.near_ptr.p + T.near_ptr_off[L],
-                                            T.near_idx.p + T.near_off[L], acc.p);
+    T.near_cnt.alloc(CL);
+    k_near_counts<<<cdiv(CL, 4), TB, 0, s>>>(T.crange.p + T.coff[L], CL, T.near_ptr.p + T.near_ptr_off[L],
+                                             T.near_idx.p + T.near_off[L], T.near_cnt.p, acc.p);
     LAUNCH_OK();
-    unsigned long long h = 0;
-    HIP_OK(hipMemcpyAsync(&h, acc.p, 8, hipMemcpyDeviceToHost, s));
+    unsigned long long h[5];
+    HIP_OK(hipMemcpyAsync(h, acc.p, sizeof(h), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));
-    T.p2p_pairs_pp = (int64_t)h;
+    for (int i = 0; i < 4; ++i) T.near_pairs[i >> 1][i & 1] = (int64_t)h[i];
+    T.near_max = (int)h[4];
+    T.p2p_pairs_pp = T.near_pairs[0][0];
   }
   // P2P chunks: at most 64 targets of one leaf per wave; a chunk of n < 64
   // targets splits the sources over 64 / n lane groups
