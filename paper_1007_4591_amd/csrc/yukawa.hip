@@ -411,7 +411,9 @@ __device__ __forceinline__ double exp_neg(double x, const double *tab) {
 // chunks): a chunk of n targets splits each near leaf's sources over
 // G = 64 / n lane groups, strided; with one group the source index is
 // uniform over the wave and the source records come through the scalar
-// cache.  The G partial sums are added in group order through LDS.
+// cache.  The G partial sums are added in group order through LDS.  As in the
+// Laplace near field, a chunk's sources are split into nseg equal parts, one
+// wave each, whose results k_lpb_combine adds in order.
 __device__ __forceinline__ void lpb_pair(double tx, double ty, double tz, double ntx, double nty, double ntz, double4 cj,
                                          double4 nj, double2 w, double kappa, double eps, double ieps,
                                          const double *tab, double &su, double &sv) {
@@ -437,11 +439,14 @@ __global__ void __launch_bounds__(64) k_lpb_near(const int4 *__restrict__ chunks
                                                  const double4 *__restrict__ nrm, const double2 *__restrict__ uvs,
                                                  const int4 *__restrict__ leaf_range,
                                                  const int32_t *__restrict__ near_ptr,
-                                                 const int32_t *__restrict__ near_idx, double kappa, double eps,
-                                                 double2 *__restrict__ out) {
+                                                 const int32_t *__restrict__ near_idx,
+                                                 const int2 *__restrict__ near_cnt, int nseg, int64_t N, double kappa,
+                                                 double eps, double2 *__restrict__ out) {
   __shared__ double2 red[64];
   __shared__ double tab[64];
-  const int4 ch = chunks[blockIdx.x];
+  const int task = xcd_block(blockIdx.x, gridDim.x);
+  const int ci = task / nseg, seg = task - ci * nseg;
+  const int4 ch = chunks[ci];
   const int leaf = ch.x, count = ch.z, G = ch.w;
   const int lane = threadIdx.x;
   tab[lane] = exp2(-lane / 64.0);
@@ -452,22 +457,50 @@ __global__ void __launch_bounds__(64) k_lpb_near(const int4 *__restrict__ chunks
   const double4 ct = ca[ti], nt = nrm[ti];
   const double ieps = 1.0 / eps;
   double su = 0.0, sv = 0.0;
-  for (int e = near_ptr[leaf]; e < near_ptr[leaf + 1]; ++e) {
-    const int4 rg = leaf_range[near_idx[e]];
-    if (G == 1) {
-      for (int j = rg.x; j < rg.y; ++j) {
-        const double4 cj = ca[j], nj = nrm[j];
-        const double2 w = uvs[j];
-        if (j != ti) lpb_pair(ct.x, ct.y, ct.z, nt.x, nt.y, nt.z, cj, nj, w, kappa, eps, ieps, tab, su, sv);
-      }
-    } else if (active) {
-      for (int j = rg.x + g; j < rg.y; j += G) {
-        if (j == ti) continue;
-        lpb_pair(ct.x, ct.y, ct.z, nt.x, nt.y, nt.z, ca[j], nrm[j], uvs[j], kappa, eps, ieps, tab, su, sv);
+  auto pair = [&](const double4 &cj, const double4 &nj, const double2 &w) {
+    lpb_pair(ct.x, ct.y, ct.z, nt.x, nt.y, nt.z, cj, nj, w, kappa, eps, ieps, tab, su, sv);
+  };
+  const int e0 = near_ptr[leaf], e1 = near_ptr[leaf + 1];
+  const int64_t total = near_cnt[leaf].x;
+  const int lo = (int)(total * seg / nseg), hi = (int)(total * (seg + 1) / nseg);
+  int seen = 0;
+  for (int eb = e0; eb < e1 && seen < hi; eb += 64) {
+    int l_sl, l_b, l_n;
+    unsigned long long todo = near_batch<false>(leaf_range, near_idx, eb, e1, false, lo, hi, seen, l_sl, l_b, l_n);
+    while (todo) {
+      const int k = __builtin_ctzll(todo);
+      todo &= todo - 1;
+      const int sl = __builtin_amdgcn_readlane(l_sl, k);
+      const int sb = __builtin_amdgcn_readlane(l_b, k);
+      const int se = sb + __builtin_amdgcn_readlane(l_n, k);
+      if (G == 1) {
+        if (sl == leaf) {
+          for (int j = sb; j < se; ++j)
+            if (j != ti) pair(ca[j], nrm[j], uvs[j]);
+        } else {
+          // the next record is requested before the current one is evaluated
+          double4 cj = ca[sb], nj = nrm[sb];
+          double2 w = uvs[sb];
+          for (int j = sb; j < se; ++j) {
+            const int jn = min(j + 1, se - 1);
+            const double4 cn = ca[jn], nn = nrm[jn];
+            const double2 wn = uvs[jn];
+            pair(cj, nj, w);
+            cj = cn;
+            nj = nn;
+            w = wn;
+          }
+        }
+      } else if (active) {
+        for (int j = sb + g; j < se; j += G) {
+          if (j == ti) continue;
+          pair(ca[j], nrm[j], uvs[j]);
+        }
       }
     }
   }
   const double q4 = 1.0 / (4.0 * PI);
+  out += (size_t)seg * N;
   if (G == 1) {
     if (active) out[ti] = make_double2(q4 * su, q4 * sv);
     return;
@@ -537,14 +570,20 @@ __global__ void k_lpb_pack(int64_t N, const int32_t *__restrict__ perm, const do
 
 __global__ void k_lpb_combine(int64_t N, const int32_t *__restrict__ perm, const double *__restrict__ uv,
                               const double *__restrict__ lap4, const double *__restrict__ nrm,
-                              const double2 *__restrict__ yk, const double2 *__restrict__ nr,
+                              const double2 *__restrict__ yk, const double2 *__restrict__ nr, int nseg,
                               const double *__restrict__ sv, const double *__restrict__ sd, double eps,
                               double *__restrict__ y) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= N) return;
   const int64_t u = perm[t];
   const double uu = uv[u], vv = uv[N + u];
-  const double2 k = yk ? yk[t] : make_double2(0.0, 0.0), n = nr[t];
+  const double2 k = yk ? yk[t] : make_double2(0.0, 0.0);
+  double2 n = nr[t];
+  for (int q = 1; q < nseg; ++q) {  // the near field's parts in order
+    const double2 o = nr[(size_t)q * N + t];
+    n.x += o.x;
+    n.y += o.y;
+  }
   const double ngrad0 = nrm[3 * u] * lap4[4 * u + 1] + nrm[3 * u + 1] * lap4[4 * u + 2] + nrm[3 * u + 2] * lap4[4 * u + 3];
   y[u] = 0.5 * (1.0 + eps) * uu - lap4[4 * u] + k.x + n.x - sv[u] * vv;
   y[N + u] = 0.5 * (1.0 + 1.0 / eps) * vv - ngrad0 + k.y / eps + n.y + sd[u] * uu;
@@ -566,12 +605,13 @@ struct LpbState {
   double kappa = -1.0;
   bool ready = false;
   int noff = 0, nlev = 0;           // M2L levels 2..L
+  int nseg = 1;                     // parts of the near field
   int64_t m2m_base = 0, l2l_base = 0, nslots = 0;
   DBuf<double> tables;              // [nslots][ps * ps], MFMA B-operand order
   Tree::M2LList list;               // panel -> panel M2L pairs grouped by (level, offset)
   DBuf<double> M, Lx, m2l_out, rows;
   DBuf<double4> ca;                 // sorted (centroid, area)
-  DBuf<double2> w, uvs, yk, nr;    // uvs: sorted (a u, a v)
+  DBuf<double2> w, uvs, yk, nr;    // uvs: sorted (a u, a v); nr: [nseg][N]
   DBuf<double> lap4, wd0, sv, sd, b, r;
   DBuf<double4> quad;
   DBuf<YkTask> tasks;
@@ -648,6 +688,7 @@ void build_level_list(Tree &T, LpbState &S, hipStream_t s) {
 
 void lpb_setup(Tree &T, double kappa, hipStream_t s) {
   set_yk_constants();
+  fmm_init(T);
   if (!T.lpb) T.lpb = new LpbState();
   LpbState &S = *T.lpb;
   const int ps = T.ps, L = T.L;
@@ -666,7 +707,8 @@ void lpb_setup(Tree &T, double kappa, hipStream_t s) {
     S.w.alloc(N);
     S.uvs.alloc(N);
     S.yk.alloc(N);
-    S.nr.alloc(N);
+    S.nseg = near_parts(T, false, false, T.nchunk_p, true, 1);
+    S.nr.alloc((size_t)S.nseg * N);
     S.lap4.alloc(4 * N);
     S.wd0.alloc(N);
     S.sv.alloc(N);
@@ -766,21 +808,30 @@ void lpb_matvec(Tree &T, double kappa, const double *uv, double *y, hipStream_t 
   const int TB = 256;
   k_lpb_pack<<<cdiv(N, TB), TB, 0, s>>>(N, T.pperm.p, T.c.p, T.area.p, uv, eps, S.ca.p, S.w.p, S.uvs.p, S.wd0.p);
   LAUNCH_OK();
-  // Laplace far field: P0 = SL0(a v) - DL0(a u), potential and gradient
+  // The near field, bound by FP64 vector work, runs on the second stream beside
+  // the far fields, whose kernels are MFMA-bound (M2L) or too small to fill the
+  // chip (the per-level ones).
+  const int L = T.L;
+  const hipStream_t ss = T.concurrent ? T.side_stream : s;
+  if (T.nchunk_p > 0) {
+    HIP_OK(hipEventRecord(T.ev_fork, s));
+    HIP_OK(hipStreamWaitEvent(ss, T.ev_fork, 0));
+    k_lpb_near<<<(unsigned)(T.nchunk_p * S.nseg), 64, 0, ss>>>(
+        T.chunk_p.p, S.ca.p, T.p64nrm.p, S.uvs.p, T.crange.p + T.coff[L], T.near_ptr.p + T.near_ptr_off[L],
+        T.near_idx.p + T.near_off[L], T.near_cnt.p, S.nseg, N, kappa, eps, S.nr.p);
+    LAUNCH_OK();
+    HIP_OK(hipEventRecord(T.ev_join, ss));
+  }
+  // Laplace far field: P0 = SL0(a v) - DL0(a u), potential and gradient (a
+  // far-field-only product leaves the fork and join events alone)
   FmmRequest rq{SRC_PANEL_MONODIP, TGT_PANEL, OUT_POTGRAD, uv + N, S.wd0.p, true, nullptr, 0.0, 1.0, false,
                 S.lap4.p, false};
   rq.far_only = true;
   fmm_apply(T, BEMFMM_FP64, rq, s);
   const bool far = T.L >= 2 && S.list.n > 0;
   if (far) yukawa_far(T, S, kappa, s);
-  const int L = T.L;
-  if (T.nchunk_p > 0) {
-    k_lpb_near<<<(unsigned)T.nchunk_p, 64, 0, s>>>(T.chunk_p.p, S.ca.p, T.p64nrm.p, S.uvs.p, T.crange.p + T.coff[L],
-                                                   T.near_ptr.p + T.near_ptr_off[L], T.near_idx.p + T.near_off[L],
-                                                   kappa, eps, S.nr.p);
-    LAUNCH_OK();
-  }
-  k_lpb_combine<<<cdiv(N, TB), TB, 0, s>>>(N, T.pperm.p, uv, S.lap4.p, T.nrm.p, far ? S.yk.p : nullptr, S.nr.p,
+  if (T.nchunk_p > 0) HIP_OK(hipStreamWaitEvent(s, T.ev_join, 0));
+  k_lpb_combine<<<cdiv(N, TB), TB, 0, s>>>(N, T.pperm.p, uv, S.lap4.p, T.nrm.p, far ? S.yk.p : nullptr, S.nr.p, S.nseg,
                                            S.sv.p, S.sd.p, eps, y);
   LAUNCH_OK();
 }
