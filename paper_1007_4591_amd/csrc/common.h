@@ -40,7 +40,7 @@ constexpr int M2L_ROWS32 = 4 * M2L_RT32 * 16, M2L_ROWS64 = 4 * M2L_RT64 * 16;
 // row tiles per wave of the persistent FP32 M2L (a tile list tile is split into
 // units of 4 * M2L_PERS_RT * 16 rows)
 constexpr int M2L_PERS_RT = 2;
-constexpr int LEVEL_RT = 1, LEVEL_ROWS = 4 * LEVEL_RT * 16;  // per-level M2M and L2L tiles
+constexpr int LEVEL_ROWS = 64;  // rows of a per-level M2M or L2L tile (four workgroups of 16)
 constexpr double PI = 3.14159265358979323846;
 constexpr double K_COULOMB = 332.06;
 
@@ -297,8 +297,7 @@ struct Tree {
   // are [t0[l], t1[l]) in both precisions.
   struct L2LList {
     DBuf<int32_t> src, self, dest, group_off, group_end;
-    // tiles of 64 rows (4 waves x one row tile of 16): the per-level products
-    // are small, so short tiles give more workgroups and shorter MFMA chains
+    // tiles of 64 rows, four workgroups of 16 rows each
     DBuf<int32_t> tile_group, tile_row;
     std::vector<int64_t> t0, t1;
     int64_t max_cells = 0;
@@ -377,7 +376,7 @@ void radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, int bits, hipStrea
 // fmm.hip
 // parts the near field of a target chunk is split into, one wave each, for
 // products that keep `sums` near sums per target
-int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, bool f64, int sums);
+int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, int sums);
 
 enum SrcKind { SRC_PANEL_MONO = 0, SRC_PANEL_DIP = 1, SRC_PANEL_MONODIP = 2, SRC_CHARGE_MONO = 3 };
 enum TgtKind { TGT_PANEL = 0, TGT_CHARGE = 1 };

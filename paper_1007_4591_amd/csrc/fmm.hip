@@ -371,19 +371,16 @@ __global__ void k_m2m_sum(int ps, int64_t cp0, int64_t CP, int64_t cl0, const in
 // source row: at k-step kk, lane group g = lane/16 supplies input g*KK + kk
 // (the B table is stored in that order).  Rows past the end of the group
 // repeat its last row (MFMA rows are independent; they are not stored).
-// The same kernel runs the batched per-level M2M and L2L products (one
-// octant operator per group); USE only names the instance (0: M2L, 1: L2L,
-// 2: M2M) so that profiles tell them apart.
 // Registers are budgeted for two waves per SIMD so that one wave's gather
 // overlaps the other's MFMA work.  With BLDS the four waves of a tile share
 // the operator through LDS instead of each reading it from L2.
 // Each result row goes to dest[row]: for M2L its place in pair order
 // (level, target, source), so that the downward pass reads a cell's rows as
-// one contiguous run; for M2M and L2L the cell's index within its level.
+// one contiguous run.
 // Output layouts (checked on the device): FP32 16x16x4 puts
 // D[4*(lane/16) + q][lane%16] in register q; FP64 16x16x4 puts
 // D[lane/16 + 4*q][lane%16] in register q.
-template <class R, int NT, int RT, bool BLDS, int USE>
+template <class R, int NT, int RT, bool BLDS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_m2l(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_row,
       const int32_t *__restrict__ group_off, const int32_t *__restrict__ group_end, const int32_t *__restrict__ src,
@@ -483,6 +480,69 @@ k_m2l(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_r
         for (int ct = 0; ct < NT; ++ct) o[ct * 16] = acc[rt][ct][q];
       }
     }
+}
+
+// The batched per-level M2M and L2L products: rows are the cells of a level
+// grouped by octant, one operator per octant (group).  A workgroup takes 16
+// rows; its 4 waves share them and split the column tiles (wave w takes ct = w,
+// w + 4), so a wave's chain is ceil(NT / 4) KK products instead of NT KK and a
+// level gives four times the workgroups.  The levels are small (24 tiles of 64
+// rows at 1,332 cells), and the chain and the operator's loads bound them: with
+// one wave per 16 rows and all column tiles a product took 20-22 us in FP64 and
+// 9.5 us in FP32 at these sizes, now 7-8.5 and 8 us.  Operand layouts and K order
+// are those of k_m2l, and so are the results, bit by bit.  USE only names the
+// instance (1: L2L, 2: M2M) so that profiles tell them apart.
+template <class R, int NT, int USE>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3)))
+k_level(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_row,
+        const int32_t *__restrict__ group_off, const int32_t *__restrict__ group_end, const int32_t *__restrict__ src,
+        const int32_t *__restrict__ dest, const R *__restrict__ Tsw, const R *__restrict__ M, R *__restrict__ out) {
+  constexpr bool F64 = sizeof(R) == 8;
+  constexpr int W = 16 / sizeof(R);
+  constexpr int PS = NT * 16;
+  constexpr int KK = PS / 4;
+  constexpr int TB = KK * NT * 64;     // reals of one octant's operator
+  constexpr int NCT = (NT + 3) / 4;    // column tiles per wave
+  using V16 = typename std::conditional<F64, double2, float4>::type;
+  using Acc = typename std::conditional<F64, f64x4, f32x4>::type;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tile = blockIdx.x >> 2;  // tiles of 64 rows
+  const int g = tile_group[tile];
+  const int end = group_end[g];
+  const int row0 = tile_row[tile] + (blockIdx.x & 3) * 16;
+  if (row0 >= end || wave >= NT) return;
+  const int i = lane & 15, kq = lane >> 4;
+  const R *B = Tsw + (size_t)group_off[g] * TB + lane;
+  const int sr = src[min(row0 + i, end - 1)];
+  const V16 *Ms = reinterpret_cast<const V16 *>(M + (size_t)sr * PS + kq * KK);
+  V16 a[KK / W];
+#pragma unroll
+  for (int v = 0; v < KK / W; ++v) a[v] = Ms[v];
+  Acc acc[NCT];
+#pragma unroll
+  for (int c = 0; c < NCT; ++c) acc[c] = Acc{0, 0, 0, 0};
+#pragma unroll
+  for (int kk = 0; kk < kk_used(NT); ++kk) {
+    const R x = reinterpret_cast<const R *>(a)[kk];
+#pragma unroll
+    for (int c = 0; c < NCT; ++c) {
+      const int ct = min(wave + 4 * c, NT - 1);  // past the last tile: repeated, not stored
+      const R b = B[(kk * NT + ct) * 64];
+      if constexpr (F64)
+        acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, b, acc[c], 0, 0, 0);
+      else
+        acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, b, acc[c], 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int rr = row0 + (F64 ? kq + 4 * q : 4 * kq + q);
+    if (rr >= end) continue;
+    R *o = out + (size_t)dest[rr] * PS + i;
+#pragma unroll
+    for (int c = 0; c < NCT; ++c)
+      if (wave + 4 * c < NT) o[(wave + 4 * c) * 16] = acc[c][q];
+  }
 }
 
 // Persistent FP32 M2L.  A workgroup (4 waves, one per SIMD) walks a
@@ -939,7 +999,7 @@ static_assert(M2LBf<NT_FIXED, RB_FIXED>::CS == P_FIXED * P_FIXED, "compact rows 
 // each with RT = 2 row tiles: 256 rows per tile, the FP32 tile lists) and
 // walks a contiguous, XCD-aware range of tiles, reloading the operator only
 // when the offset group changes.  Per tile the arithmetic is that of
-// k_m2l<double, NT, 2, false, 0> (same operands, same K order), so results
+// k_m2l<double, NT, 2, false> (same operands, same K order), so results
 // are identical; the operator is read from LDS instead of from L2 at every
 // k-step.
 template <int NT>
@@ -1975,20 +2035,17 @@ static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
 // 153 us.
 // One sum per target (the potential) gains throughout: FP32 A^T at 128,000
 // panels 603 -> 533 us, at 327,680 981 -> 917 us.  With the three of a
-// gradient, parts stop where they cost more than they give.  FP32 parts store
-// them per target and near leaf: at more than one chunk per SIMD that pays for
-// long lists only (FP32 A, 62,720 and 184,320 panels, 2,100 and 1,400 sources per
-// target: 264 -> 290 and 541 -> 612 us; 128,000 panels, 4,400 sources: 584 -> 508
-// us).  In FP64 it is the waves beside the M2L that cost: at 4 chunks per SIMD
-// and below parts gain (FP64 A, 81,920 and 128,000 panels: 637 -> 571 and 1099 ->
-// 857 us), above they lose (184,320 and 327,680: 1248 -> 1287 and 1846 -> 1887 us).
-int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, bool f64, int sums) {
-  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32, LONG_LIST = 3500;
-  if (nchunks <= 0) return 1;
+// gradient, parts gain up to 4 chunks per SIMD (FP32 A at 46,080 and 62,720
+// panels 266 -> 217 and 327 -> 243 us; FP64 A at 81,920 and 128,000 panels 637 ->
+// 571 and 1099 -> 857 us) and lose above, where FP32 writes three totals per
+// target and near leaf, and FP64 holds up the M2L beside it (184,320 panels:
+// FP32 559 -> 604, FP64 1248 -> 1287 us).
+int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, int sums) {
+  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32;
   const int64_t simds = 4 * (int64_t)T.n_cu;
+  if (nchunks <= 0 || (sums > 1 && nchunks > 4 * simds)) return 1;
   const int64_t npts = std::max<int64_t>(tgt_charges ? T.Q : T.N, 1);
   const int64_t mean = T.near_pairs[src_charges][tgt_charges] / npts;  // sources per target
-  if (sums > 1 && (f64 ? nchunks > 4 * simds : nchunks > simds && mean < LONG_LIST)) return 1;
   const int64_t want = cdiv(WAVES_PER_SIMD * simds, nchunks);
   return (int)std::max<int64_t>(1, std::min(std::min(want, mean / MIN_SOURCES), MAX_PARTS));
 }
@@ -2050,19 +2107,12 @@ static void level_product(Tree &T, int l, const int32_t *src, const void *table,
   const Tree::L2LList &LW = T.l2lw;
   const int64_t t0 = LW.t0[l], t1 = LW.t1[l];
   if (t1 <= t0) return;
-  const dim3 grid((unsigned)(t1 - t0));
+  const dim3 grid((unsigned)(4 * (t1 - t0)));  // 16 rows each
 #define LEVEL_CASE(nt)                                                                                          \
   case nt:                                                                                                      \
-    if (f64)                                                                                                    \
-      k_m2l<double, nt, LEVEL_RT, false, USE><<<grid, 256, 0, s>>>(                                             \
-          LW.tile_group.p + t0, LW.tile_row.p + t0, LW.group_off.p, LW.group_end.p, src, LW.dest.p,             \
-          reinterpret_cast<const double *>(table), reinterpret_cast<const double *>(in),                        \
-          reinterpret_cast<double *>(out));                                                                     \
-    else                                                                                                        \
-      k_m2l<float, nt, LEVEL_RT, true, USE><<<grid, 256, 0, s>>>(                                               \
-          LW.tile_group.p + t0, LW.tile_row.p + t0, LW.group_off.p, LW.group_end.p, src, LW.dest.p,             \
-          reinterpret_cast<const float *>(table), reinterpret_cast<const float *>(in),                          \
-          reinterpret_cast<float *>(out));                                                                      \
+    k_level<R, nt, USE><<<grid, 256, 0, s>>>(LW.tile_group.p + t0, LW.tile_row.p + t0, LW.group_off.p,           \
+                                             LW.group_end.p, src, LW.dest.p, reinterpret_cast<const R *>(table), \
+                                             in, out);                                                          \
     break;
   switch (T.ps / 16) {
     LEVEL_CASE(1)
@@ -2145,7 +2195,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   a.dbg_far = T.debug_record ? B.dbg_far.p : nullptr;
   B.dbg_valid = T.debug_record;
   a.near_cnt = T.near_cnt.p;
-  a.nseg = rq.far_only ? 1 : near_parts(T, src_charges, tgt_ch, nchunks, f64, near_ncomp(rq.out));
+  a.nseg = rq.far_only ? 1 : near_parts(T, src_charges, tgt_ch, nchunks, near_ncomp(rq.out));
   a.nsum = f64 ? a.nseg : 1;
   const int64_t ntgt = tgt_ch ? T.Q : T.N;
   a.seg_stride = (size_t)ntgt * (rq.out == OUT_POTGRAD ? 4 : 1);
@@ -2257,7 +2307,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l64,      \
           reinterpret_cast<const double *>(M), reinterpret_cast<double *>(m2l), (int)ML.ntiles);               \
     else if (f64)                                                                                              \
-      k_m2l<double, nt, M2L_RT64, false, 0><<<dim3((unsigned)ML.ntiles64), 256, 0, s>>>(                         \
+      k_m2l<double, nt, M2L_RT64, false><<<dim3((unsigned)ML.ntiles64), 256, 0, s>>>(                         \
           ML.tile_group64.p, ML.tile_row64.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l64,             \
           reinterpret_cast<const double *>(M), reinterpret_cast<double *>(m2l));                               \
     else if (T.m2l_persistent)                                                                                  \
@@ -2266,7 +2316,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l32,      \
           reinterpret_cast<const float *>(M), reinterpret_cast<float *>(m2l), (int)ML.ntiles);                 \
     else                                                                                                       \
-      k_m2l<float, nt, M2L_RT32, true, 0><<<dim3((unsigned)ML.ntiles), 256, 0, s>>>(                              \
+      k_m2l<float, nt, M2L_RT32, true><<<dim3((unsigned)ML.ntiles), 256, 0, s>>>(                              \
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l32,                 \
           reinterpret_cast<const float *>(M), reinterpret_cast<float *>(m2l));                                 \
     break;
@@ -2397,7 +2447,7 @@ void m2l_tiles64(const Tree::M2LList &ML, int ps, const double *table, const dou
   const dim3 grid((unsigned)ML.ntiles64);
 #define M2L64_CASE(nt)                                                                                      \
   case nt:                                                                                                  \
-    k_m2l<double, nt, M2L_RT64, false, 0><<<grid, 256, 0, s>>>(ML.tile_group64.p, ML.tile_row64.p,         \
+    k_m2l<double, nt, M2L_RT64, false><<<grid, 256, 0, s>>>(ML.tile_group64.p, ML.tile_row64.p,         \
                                                                 ML.group_off.p, ML.group_end.p, ML.src.p,  \
                                                                 ML.dest.p, table, M, out);                 \
     break;
