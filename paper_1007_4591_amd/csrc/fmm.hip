@@ -2206,14 +2206,15 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   a.near_out = rq.far_only ? nullptr : B.near_out.p;
   B.last_tgt = rq.tgt;
   // The near field runs on the second stream, forked from the caller's
-  // stream at a point of the upward pass and joined before L2P.  It forks
-  // after P2M, except for an M2L large enough to keep persistent workgroups
-  // busy for a while (at least 32 tiles of 256 pairs per CU; 8 for the
-  // split-bf16 M2L, whose waves leave room for near-field waves): that M2L
-  // runs persistent (in FP64 too) and the fork comes after M2M, so that the
-  // M2L workgroups are resident before near-field waves fill the chip, and
-  // the near field takes the rest.  Smaller M2L runs one tile per workgroup
-  // in FP64.
+  // stream at a point of the upward pass and joined before L2P.  In FP32 and
+  // with a persistent M2L (FP64: at least 32 tiles of 256 pairs per CU) it
+  // forks after M2M: the few small kernels of the M2M would wait for near-field
+  // waves to retire, and the M2L's workgroups are resident first.  Forked after
+  // P2M instead, the FP32 A product takes 339 instead of 303 us at 81,920
+  // panels and 1032 instead of 941 us at 327,680, and A^T 217 instead of 184 us at
+  // 46,080.  The smaller FP64 M2L runs one tile per workgroup, which near-field
+  // waves hold up wherever they start; after P2M is the better there (327,680
+  // panels 1.83 against 1.85 ms).
   const hipStream_t ss = T.concurrent ? T.side_stream : s;
   const int combo = src_charges ? 1 : (rq.tgt == TGT_CHARGE ? 2 : 0);
   const Tree::M2LList &ML = T.m2l[combo];
@@ -2223,11 +2224,10 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   // agrees with the FP32 MFMA kernel to about 1e-9.  Products from or to
   // charges keep the FP32 MFMA kernel: their FP32 sums are more sensitive
   // (an energy sums them over the charges), and they are a small part of a
-  // solve.  It leaves registers for near-field waves beside it, so it gains
-  // from going first from 8 tiles per CU on (the others from 32).
+  // solve.
   const bool split_m2l =
       !f64 && combo == 0 && T.m2l_persistent && T.m2l_split && T.p == P_FIXED && T.t_m2lbf;
-  const bool m2l_first = split_m2l ? ML.ntiles >= 8 * (int64_t)T.n_cu : big_m2l;
+  const bool m2l_first = !f64 || big_m2l;
   // M2L result rows without the padding places (read so by the downward pass)
   const bool compact_rows = split_m2l;
   const int fork_at = !far ? FORK_START : T.fork_at >= 0 ? T.fork_at : (m2l_first ? FORK_AFTER_M2M : FORK_AFTER_P2M);
