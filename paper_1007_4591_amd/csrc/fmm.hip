@@ -2231,10 +2231,11 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   // M2L result rows without the padding places (read so by the downward pass)
   const bool compact_rows = split_m2l;
   const int fork_at = !far ? FORK_START : T.fork_at >= 0 ? T.fork_at : (m2l_first ? FORK_AFTER_M2M : FORK_AFTER_P2M);
-  auto fork_near = [&]() {
-    if (rq.far_only) return;
-    HIP_OK(hipEventRecord(T.ev_fork, s));
-    if (nchunks > 0) {
+  auto fork_point = [&]() {
+    if (!rq.far_only) HIP_OK(hipEventRecord(T.ev_fork, s));
+  };
+  auto launch_near = [&]() {
+    if (!rq.far_only && nchunks > 0) {
       HIP_OK(hipStreamWaitEvent(ss, T.ev_fork, 0));
       const P2PArgs &ap = a;
       const unsigned nb = (unsigned)(nchunks * a.nseg);
@@ -2274,6 +2275,10 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
       HIP_OK(hipEventRecord(T.ev_join, ss));
     }
   };
+  auto fork_near = [&]() {
+    fork_point();
+    launch_near();
+  };
   if (fork_at == FORK_START) fork_near();
 
   if (far) {
@@ -2293,7 +2298,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
       LAUNCH_OK();
     }
     prof_end(T, ST_M2M, s);
-    if (fork_at == FORK_AFTER_M2M) fork_near();
+    if (fork_at == FORK_AFTER_M2M) fork_point();
   }
   if (far) {
     // M2L, every level in one launch
@@ -2342,6 +2347,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
       LAUNCH_OK();
     }
     prof_end(T, ST_M2L, s);
+    if (fork_at == FORK_AFTER_M2M) launch_near();
     if (fork_at == FORK_AFTER_M2L) fork_near();
     // downward pass, levels 2 .. L
     prof_begin(T, ST_L2L, s);
