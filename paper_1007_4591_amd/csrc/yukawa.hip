@@ -114,6 +114,9 @@ void gauss_legendre(int n, std::vector<double> &x, std::vector<double> &w) {
   }
 }
 
+// reals of a lane's row of partial coefficients in LDS
+__host__ __device__ inline int yk_row(int p) { return (p * p) | 1; }
+
 // normalisation of the real harmonics: sqrt((2n+1)/(4 pi) (n-m)!/(n+m)!), times sqrt 2 for m > 0
 double ynorm(int n, int m) {
   double r = (2 * n + 1) / (4.0 * PI);
@@ -150,11 +153,15 @@ void set_yk_constants() {
 
 // R_nm = rho^n Y_nm at (x, y, z) for n < p; with DER also the derivative
 // along (dx, dy, dz).  term(k, n, value, derivative) for each packed index k.
-template <bool DER, class F>
-__device__ inline void yk_solid(int p, double x, double y, double z, double dx, double dy, double dz, F &&term) {
+// P > 0: the order fixed at compile time (P == p), so that the loops unroll and
+// arrays indexed by n stay in registers; P = 0: any order.
+template <int P, bool DER, class F>
+__device__ __forceinline__ void yk_solid(int p_, double x, double y, double z, double dx, double dy, double dz, F &&term) {
+  const int p = P > 0 ? P : p_;
   const double r2 = x * x + y * y + z * z;
   const double dr2 = DER ? 2.0 * (x * dx + y * dy + z * dz) : 0.0;
   double wr = 1.0, wi = 0.0, dwr = 0.0, dwi = 0.0;  // (x + i y)^m
+#pragma unroll (P > 0 ? P : 1)
   for (int m = 0; m < p; ++m) {
     if (m > 0) {
       const double nr = wr * x - wi * y, ni = wr * y + wi * x;
@@ -169,6 +176,7 @@ __device__ inline void yk_solid(int p, double x, double y, double z, double dx, 
     }
     double cr = c_yd[m] * wr, ci = c_yd[m] * wi, dcr = DER ? c_yd[m] * dwr : 0.0, dci = DER ? c_yd[m] * dwi : 0.0;
     double pr = 0.0, pi = 0.0, dpr = 0.0, dpi = 0.0;  // degree n - 1
+#pragma unroll (P > 0 ? P : 1)
     for (int n = m; n < p; ++n) {
       if (n > m) {
         const double a = c_ya[n][m], b = c_yb[n][m];
@@ -197,22 +205,40 @@ __device__ inline void yk_solid(int p, double x, double y, double z, double dx, 
   }
 }
 
-// g_n(s) and dg_n/ds at s = rho^2, n < p
-__device__ inline void yk_g(int p, double kappa, double s, double *g, double *gp) {
-  const double hk = 0.5 * kappa * kappa;
-  double pref = 1.0;
-  for (int n = 0; n < p; ++n) {
-    if (n > 0) pref *= kappa / (2 * n + 1);
-    double t = 1.0, sum = 1.0, dsum = 0.0;
+// g_n(s) and dg_n/ds at s = rho^2, n < p.  With g_n = c_n h_n, c_n = kappa^n /
+// (2n+1)!!, the recurrence of the i_n gives h_(n-1) = h_n + s kappa^2 h_(n+1) /
+// ((2n+1)(2n+3)), all terms positive, and dg_n/ds = (kappa/2) g_(n+1).  Only h_p
+// and h_(p-1) are summed as series, h_n = sum_k t_k with t_k = t_(k-1) (s
+// kappa^2/2) / (k (2n+2k+1)): a division per term, where a series per degree
+// took ten times as many.
+template <int P>
+__device__ __forceinline__ void yk_g(int p_, double kappa, double s, double *g, double *gp) {
+  const int p = P > 0 ? P : p_;
+  const double x = 0.5 * kappa * kappa * s;
+  double h[2];  // h_p, h_(p-1)
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int n = p - i;
+    double t = 1.0, sum = 1.0;
     for (int k = 1; k < 400; ++k) {
-      const double f = hk / (2 * n + 2 * k + 1);
-      dsum += t * f;  // k c_k s^(k-1) = t_(k-1) f
-      t *= f * s / k;
+      t *= x / (double)(k * (2 * n + 2 * k + 1));
       sum += t;
-      if (t <= 1e-18 * sum && t * f <= 1e-18 * dsum * s + 1e-300) break;
+      if (t <= 1e-18 * sum) break;
     }
-    g[n] = pref * sum;
-    gp[n] = pref * dsum;
+    h[i] = sum;
+  }
+  double c[PMAX + 1];
+  c[0] = 1.0;
+#pragma unroll (P > 0 ? P : 1)
+  for (int n = 1; n <= p; ++n) c[n] = c[n - 1] * (kappa / (2 * n + 1));
+  double h1 = h[0], h0 = h[1];  // h_(n+1), h_n
+#pragma unroll (P > 0 ? P : 1)
+  for (int n = p - 1; n >= 0; --n) {
+    g[n] = c[n] * h0;
+    gp[n] = 0.5 * kappa * c[n + 1] * h1;
+    const double hm = h0 + 2.0 * x * h1 / (double)((2 * n + 1) * (2 * n + 3));  // h_(n-1)
+    h1 = h0;
+    h0 = hm;
   }
 }
 
@@ -251,7 +277,7 @@ __global__ void __launch_bounds__(YK_THREADS) k_yk_project(int p, int ps, double
       yk_khat(p, kappa * tk.rho0, aux);
       for (int n = 0; n < p; ++n) norm[n] = 1.0 / (kappa * aux[n]);
     } else {
-      yk_g(p, kappa, tk.rho0 * tk.rho0, aux, aux + PMAX);
+      yk_g<0>(p, kappa, tk.rho0 * tk.rho0, aux, aux + PMAX);
       double rp = 1.0;
       for (int n = 0; n < p; ++n) {
         norm[n] = 1.0 / (aux[n] * rp);
@@ -279,15 +305,15 @@ __global__ void __launch_bounds__(YK_THREADS) k_yk_project(int p, int ps, double
         }
       } else {
         double gp[PMAX];
-        yk_g(p, kappa, r2, rd, gp);
+        yk_g<0>(p, kappa, r2, rd, gp);
       }
       double *row = Bv + tid * np2;
-      yk_solid<false>(p, x, y, z, 0.0, 0.0, 0.0, [&](int k, int n, double v, double) { row[k] = rd[n] * v; });
+      yk_solid<0, false>(p, x, y, z, 0.0, 0.0, 0.0, [&](int k, int n, double v, double) { row[k] = rd[n] * v; });
     } else if (tid < 2 * YQ_CHUNK) {
       const int q = tid - YQ_CHUNK;
       const double4 u = quad[c0 + q];
       double *row = Wv + q * np2;
-      yk_solid<false>(p, u.x, u.y, u.z, 0.0, 0.0, 0.0, [&](int k, int, double v, double) { row[k] = u.w * v; });
+      yk_solid<0, false>(p, u.x, u.y, u.z, 0.0, 0.0, 0.0, [&](int k, int, double v, double) { row[k] = u.w * v; });
     }
     __syncthreads();
     if (mine) {
@@ -320,50 +346,60 @@ __global__ void __launch_bounds__(YK_THREADS) k_yk_project(int p, int ps, double
 }
 
 // P2M of the screened kernel at the leaves: one wave per leaf, each lane
-// sums its sources into its own LDS row, then the 64 rows are added in lane
-// order.  w = (monopole weight, dipole weight along the panel normal).
-__global__ void __launch_bounds__(64) k_yk_p2m(int p, int ps, const int4 *__restrict__ leaf_range,
+// sums its sources into its own LDS row (an odd number of doubles, so that the
+// lanes fall on different banks), then the rows are added in lane order.  w =
+// (monopole weight, dipole weight along the panel normal).  Bound by the FP64
+// arithmetic of a source and, at about 50 KB of LDS per wave, by three waves
+// per CU.  At 1,332 leaves of 35 panels it took 87 us with a series per degree
+// and run-time orders, now 38 us.
+template <int P>
+__global__ void __launch_bounds__(64) k_yk_p2m(int p_, int ps, const int4 *__restrict__ leaf_range,
                                                const double4 *__restrict__ pos, const double4 *__restrict__ nrm,
                                                const double2 *__restrict__ w, double kappa, double *__restrict__ M) {
-  extern __shared__ double part[];  // [64][np2]
-  const int np2 = p * p, lane = threadIdx.x;
+  extern __shared__ double part[];  // [64][yk_row(p)]
+  const int p = P > 0 ? P : p_;
+  const int np2 = p * p, stride = yk_row(p), lane = threadIdx.x;
   const int4 rg = leaf_range[blockIdx.x];
-  double *mine = part + lane * np2;
-  for (int k = 0; k < np2; ++k) mine[k] = 0.0;
+  double *mine = part + lane * stride;
   for (int j = rg.x + lane; j < rg.y; j += 64) {
+    const bool first = j < rg.x + 64;
     const double4 r = pos[j], n4 = nrm[j];
     const double2 ww = w[j];
     double g[PMAX], gp[PMAX];
-    yk_g(p, kappa, r.x * r.x + r.y * r.y + r.z * r.z, g, gp);
-    const double nd = n4.x * r.x + n4.y * r.y + n4.z * r.z;
-    yk_solid<true>(p, r.x, r.y, r.z, n4.x, n4.y, n4.z, [&](int k, int n, double v, double dv) {
-      mine[k] += ww.x * g[n] * v + ww.y * (2.0 * gp[n] * nd * v + g[n] * dv);
+    yk_g<P>(p, kappa, r.x * r.x + r.y * r.y + r.z * r.z, g, gp);
+    const double nd2 = 2.0 * (n4.x * r.x + n4.y * r.y + n4.z * r.z);
+    yk_solid<P, true>(p, r.x, r.y, r.z, n4.x, n4.y, n4.z, [&](int k, int n, double v, double dv) {
+      const double t = ww.x * g[n] * v + ww.y * (gp[n] * nd2 * v + g[n] * dv);
+      mine[k] = first ? t : mine[k] + t;
     });
   }
   __syncthreads();
+  const int rows = min(64, rg.y - rg.x);
   double *row = M + (size_t)blockIdx.x * ps;
   for (int i = lane; i < ps; i += 64) {
     const int k = coef_at(i, p, ps);
     double s = 0.0;
     if (k >= 0)
-      for (int l = 0; l < 64; ++l) s += part[l * np2 + k];
+      for (int l = 0; l < rows; ++l) s += part[l * stride + k];
     row[i] = s;
   }
 }
 
 // L2P of the screened kernel at every panel: potential and normal derivative
-__global__ void k_yk_l2p(int p, int ps, int64_t N, const int32_t *__restrict__ pleaf, const double4 *__restrict__ pos,
+template <int P>
+__global__ void k_yk_l2p(int p_, int ps, int64_t N, const int32_t *__restrict__ pleaf, const double4 *__restrict__ pos,
                          const double4 *__restrict__ nrm, const double *__restrict__ Lleaf, double kappa,
                          double2 *__restrict__ out) {
   const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= N) return;
+  const int p = P > 0 ? P : p_;
   const double *Lr = Lleaf + (size_t)pleaf[t] * ps;
   const double4 r = pos[t], n4 = nrm[t];
   double g[PMAX], gp[PMAX];
-  yk_g(p, kappa, r.x * r.x + r.y * r.y + r.z * r.z, g, gp);
+  yk_g<P>(p, kappa, r.x * r.x + r.y * r.y + r.z * r.z, g, gp);
   const double nd = n4.x * r.x + n4.y * r.y + n4.z * r.z;
   double phi = 0.0, dphi = 0.0;
-  yk_solid<true>(p, r.x, r.y, r.z, n4.x, n4.y, n4.z, [&](int k, int n, double v, double dv) {
+  yk_solid<P, true>(p, r.x, r.y, r.z, n4.x, n4.y, n4.z, [&](int k, int n, double v, double dv) {
     const double c = Lr[coef_pos(k, p, ps)];
     phi += c * g[n] * v;
     dphi += c * (2.0 * gp[n] * nd * v + g[n] * dv);
@@ -725,8 +761,9 @@ void lpb_setup(Tree &T, double kappa, hipStream_t s) {
       }
     }
     // dynamic LDS beyond 64 KB is allowed once per kernel, here
-    HIP_OK(hipFuncSetAttribute((const void *)k_yk_p2m, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               (int)((size_t)64 * T.p * T.p * sizeof(double))));
+    HIP_OK(hipFuncSetAttribute(T.p == P_FIXED ? (const void *)k_yk_p2m<P_FIXED> : (const void *)k_yk_p2m<0>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                               (int)((size_t)64 * yk_row(T.p) * sizeof(double))));
     HIP_OK(hipFuncSetAttribute((const void *)k_yk_project, hipFuncAttributeMaxDynamicSharedMemorySize,
                                (int)(((size_t)2 * YQ_CHUNK * T.p * T.p + 2 * YQ_CHUNK * PMAX + PMAX) * sizeof(double))));
     S.quad.alloc(YQ_N);
@@ -778,8 +815,9 @@ void yukawa_far(Tree &T, LpbState &S, double kappa, hipStream_t s) {
   const int L = T.L, p = T.p, ps = T.ps;
   const int64_t CL = T.ncell[L];
   double *M = S.M.p, *Lx = S.Lx.p;
-  const size_t shm = (size_t)64 * p * p * sizeof(double);
-  k_yk_p2m<<<(unsigned)CL, 64, shm, s>>>(p, ps, T.crange.p + T.coff[L], T.p64pos.p, T.p64nrm.p, S.w.p, kappa,
+  const size_t shm = (size_t)64 * yk_row(p) * sizeof(double);
+  const auto p2m = p == P_FIXED ? k_yk_p2m<P_FIXED> : k_yk_p2m<0>;
+  p2m<<<(unsigned)CL, 64, shm, s>>>(p, ps, T.crange.p + T.coff[L], T.p64pos.p, T.p64nrm.p, S.w.p, kappa,
                                          M + (size_t)T.coff[L] * ps);
   LAUNCH_OK();
   const double *tab = S.tables.p;
@@ -793,7 +831,8 @@ void yukawa_far(Tree &T, LpbState &S, double kappa, hipStream_t s) {
       level_product64(T, l, T.l2lw.src.p, tab + (size_t)(S.l2l_base + (l - 3) * 8) * ps * ps, Lx, S.rows.p, false, s);
     downward64(T, l, S.rows.p, T.m2l[0].kptr.p, S.m2l_out.p, Lx, s);
   }
-  k_yk_l2p<<<cdiv(T.N, 128), 128, 0, s>>>(p, ps, T.N, T.pleaf.p, T.p64pos.p, T.p64nrm.p,
+  const auto l2p = p == P_FIXED ? k_yk_l2p<P_FIXED> : k_yk_l2p<0>;
+  l2p<<<cdiv(T.N, 128), 128, 0, s>>>(p, ps, T.N, T.pleaf.p, T.p64pos.p, T.p64nrm.p,
                                           Lx + (size_t)T.coff[L] * ps, kappa, S.yk.p);
   LAUNCH_OK();
 }
@@ -808,10 +847,17 @@ void lpb_matvec(Tree &T, double kappa, const double *uv, double *y, hipStream_t 
   const int TB = 256;
   k_lpb_pack<<<cdiv(N, TB), TB, 0, s>>>(N, T.pperm.p, T.c.p, T.area.p, uv, eps, S.ca.p, S.w.p, S.uvs.p, S.wd0.p);
   LAUNCH_OK();
-  // The near field, bound by FP64 vector work, runs on the second stream beside
-  // the far fields, whose kernels are MFMA-bound (M2L) or too small to fill the
-  // chip (the per-level ones).
   const int L = T.L;
+  // Laplace far field: P0 = SL0(a v) - DL0(a u), potential and gradient
+  FmmRequest rq{SRC_PANEL_MONODIP, TGT_PANEL, OUT_POTGRAD, uv + N, S.wd0.p, true, nullptr, 0.0, 1.0, false,
+                S.lap4.p, false};
+  rq.far_only = true;
+  fmm_apply(T, BEMFMM_FP64, rq, s);
+  // The near field, bound by FP64 vector work, runs on the second stream beside
+  // the screened far field, whose kernels are MFMA-bound (M2L) or too small to
+  // fill the chip (the per-level ones).  Started before the Laplace far field
+  // its waves hold up both chains (46,080 panels, solve: 17.3 against 16.8 ms),
+  // after both it has nothing beside it (19.1 ms).
   const hipStream_t ss = T.concurrent ? T.side_stream : s;
   if (T.nchunk_p > 0) {
     HIP_OK(hipEventRecord(T.ev_fork, s));
@@ -822,12 +868,6 @@ void lpb_matvec(Tree &T, double kappa, const double *uv, double *y, hipStream_t 
     LAUNCH_OK();
     HIP_OK(hipEventRecord(T.ev_join, ss));
   }
-  // Laplace far field: P0 = SL0(a v) - DL0(a u), potential and gradient (a
-  // far-field-only product leaves the fork and join events alone)
-  FmmRequest rq{SRC_PANEL_MONODIP, TGT_PANEL, OUT_POTGRAD, uv + N, S.wd0.p, true, nullptr, 0.0, 1.0, false,
-                S.lap4.p, false};
-  rq.far_only = true;
-  fmm_apply(T, BEMFMM_FP64, rq, s);
   const bool far = T.L >= 2 && S.list.n > 0;
   if (far) yukawa_far(T, S, kappa, s);
   if (T.nchunk_p > 0) HIP_OK(hipStreamWaitEvent(s, T.ev_join, 0));

@@ -101,3 +101,19 @@ def test_lpb_rejects_bad_arguments():
             B.lpb_matvec(t, kappa, z)
         assert ei.value.code == 1
     B.tree_destroy(t)
+
+
+@pytest.mark.parametrize("order,ncrit", [(10, 200), (11, 32), (11, 200)])
+def test_lpb_orders_and_long_leaves(order, ncrit):
+    """The far field's kernels of the compiled order and of any order, on
+    leaves of fewer and of more than 64 panels: the matvec bar on each half."""
+    B = lib()
+    p = synth.blobby(4, n_charges=20)                    # 5,120 panels
+    S = _oracle(p, 0.3)
+    t = B.build_tree(p.verts, p.tris, p.charge_pos, B.Params(p=order, ncrit=ncrit))
+    N = p.n_panels
+    z = np.random.default_rng(6).normal(size=2 * N)
+    y, want = host(B.lpb_matvec(t, 0.3, dev(z))), S.apply(z)
+    for h in (slice(0, N), slice(N, 2 * N)):
+        assert rel_l2(y[h], want[h]) <= 1e-5
+    B.tree_destroy(t)
