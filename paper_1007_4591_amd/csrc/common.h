@@ -417,9 +417,9 @@ double molecule_energy(Tree &T, const double *q, int method, int precision, doub
 void adjoint(Tree &T, const double *q, const double *x, double tol, int maxit, int restart, int precision,
              double *dq, double *dpos, bemfmm_solve_info *info, hipStream_t s);
 double dot_d(Tree &T, const double *a, const double *b, int64_t n, hipStream_t s);
-// GMRES(restart) from x = 0 on any operator of vectors of length n; returns the iterations
+// GMRES(restart) from x = 0 on any operator of vectors of length n, bnorm = |b|; returns the iterations
 int gmres_apply(Tree &T, const std::function<void(const double *, double *)> &A, int64_t n, const double *b,
-                double *x, double tol, int maxit, int restart, hipStream_t s);
+                double bnorm, double *x, double tol, int maxit, int restart, hipStream_t s);
 
 // FP64 building blocks of the FMM shared with the screened-kernel (Yukawa)
 // far field of yukawa.hip: the batched per-level MFMA product (M2M when m2m,

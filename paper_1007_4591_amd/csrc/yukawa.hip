@@ -882,8 +882,8 @@ void lpb_solve(Tree &T, const double *q, double kappa, double *uv, double tol, i
   lpb_setup(T, kappa, s);
   LpbState &S = *T.lpb;
   const int64_t N = T.N;
-  S.b.alloc(2 * N);
-  S.r.alloc(2 * N);
+  S.b.reserve(2 * N);
+  S.r.reserve(2 * N);
   // right-hand side [S; dS/dn]: the charges' potential and normal field over eps_in
   if (T.Q > 0) {
     FmmRequest r1{SRC_CHARGE_MONO, TGT_PANEL, OUT_POT, q, nullptr, false, nullptr, 0.0, 1.0 / T.prm.eps_in, false,
@@ -899,7 +899,7 @@ void lpb_solve(Tree &T, const double *q, double kappa, double *uv, double tol, i
   bemfmm_solve_info inf{};
   inf.outer_iters = 1;
   const double bn = std::sqrt(dot_d(T, S.b.p, S.b.p, 2 * N, s));
-  inf.iters = gmres_apply(T, A, 2 * N, S.b.p, uv, tol, maxit, restart, s);
+  inf.iters = gmres_apply(T, A, 2 * N, S.b.p, bn, uv, tol, maxit, restart, s);
   if (bn > 0.0) {
     A(uv, S.r.p);
     k_sub2<<<cdiv(2 * N, 256), 256, 0, s>>>(S.r.p, S.b.p, S.r.p, 2 * N);
@@ -918,10 +918,10 @@ double lpb_energy(Tree &T, const double *q, const double *uv, hipStream_t s) {
   if (!T.lpb) T.lpb = new LpbState();
   LpbState &S = *T.lpb;
   const int64_t N = T.N;
-  S.wd0.alloc(N);
-  S.r.alloc(std::max<int64_t>(2 * N, T.Q));
-  S.w.alloc(N);
-  S.uvs.alloc(N);
+  S.wd0.reserve(N);
+  S.r.reserve(std::max<int64_t>(2 * N, T.Q));
+  S.w.reserve(N);
+  S.uvs.reserve(N);
   // dipole weights -a u (the packing's sorted outputs are not needed here)
   k_lpb_pack<<<cdiv(N, 256), 256, 0, s>>>(N, T.pperm.p, T.c.p, T.area.p, uv, 1.0, nullptr, S.w.p, S.uvs.p, S.wd0.p);
   LAUNCH_OK();
