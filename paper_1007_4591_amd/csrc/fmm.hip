@@ -45,6 +45,7 @@ struct PrecBufs {
   DBuf<double> dbg_near, dbg_far;  // sorted-order raw fields (only while debug recording is on)
   bool dbg_valid = false;          // the last product recorded them
   DBuf<double> near_out;           // near field per target (sorted order), per part
+  DBuf<double> nq_out;             // near quadrature per target (sorted order)
   DBuf<float> leaf_out;            // FP32 near field of several parts: leaf totals per lane
   int last_tgt = 0;
   bool have = false;
@@ -1337,21 +1338,40 @@ __device__ __forceinline__ void pair_accumulate(const typename V4<R>::T &s4, con
   pair_eval_r2<R, SRC, OUT>(s4, m4, dx, dy, dz, r2, skip, lp, lx, ly, lz);
 }
 
-// Near quadrature: near_out[t] += sum over the close pairs of t, in list
-// order, of coef * x[caller index] (FP64; 4 pi times the exact-minus-point
-// difference of K' or of K'^T, see the tree's nq lists).  For A^T the sum is
-// divided by the target's area as the product stores it (the combine
-// multiplies the near field by that same area).
+// Near quadrature: out[t] = sum over the close pairs of t, in list order, of
+// coef * x[caller index] (FP64; 4 pi times the exact-minus-point difference of
+// K' or of K'^T, see the tree's nq lists), which the combine adds to the near
+// field.  For A^T the sum is divided by the target's area as the product
+// stores it (the combine multiplies the near field by that same area).
+// Bound by memory: 12 bytes per pair, in runs, and x at about 11 places per
+// row.  A workgroup takes 256 rows, one run of the list: its coefficients and
+// values are loaded 2048 at a time in runs and go through LDS, where each thread
+// adds its own row in order.  With a thread reading its own row the kernel took 170
+// us at 655,220 panels (7.5 million pairs), and ran after the near field; now 91
+// us, beside the upward pass.
 template <class R>
-__global__ void k_nq_apply(int64_t n, const int32_t *__restrict__ ptr, const int32_t *__restrict__ idx,
-                           const double *__restrict__ coef, const double *__restrict__ x,
-                           const typename V4<R>::T *__restrict__ tgt_pos, double *__restrict__ near_out) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n) return;
+__global__ void __launch_bounds__(256) k_nq_apply(int64_t n, const int32_t *__restrict__ ptr,
+                                                  const int32_t *__restrict__ idx, const double *__restrict__ coef,
+                                                  const double *__restrict__ x,
+                                                  const typename V4<R>::T *__restrict__ tgt_pos,
+                                                  double *__restrict__ out) {
+  constexpr int TILE = 2048;
+  __shared__ double2 pair[TILE];
+  const int64_t t0 = (int64_t)blockIdx.x * 256, t = t0 + threadIdx.x;
+  const int b = ptr[t0], e = ptr[min(t0 + 256, n)];
+  int k = t < n ? ptr[t] : 0;
+  const int ke = t < n ? ptr[t + 1] : 0;
   double acc = 0.0;
-  for (int k = ptr[t]; k < ptr[t + 1]; ++k) acc += coef[k] * x[idx[k]];
+  for (int base = b; base < e; base += TILE) {
+    const int end = min(base + TILE, e);
+    __syncthreads();  // the previous pairs are no longer read
+    for (int i = base + threadIdx.x; i < end; i += 256) pair[i - base] = make_double2(coef[i], x[idx[i]]);
+    __syncthreads();
+    for (; k < min(ke, end); ++k) acc = fma_(pair[k - base].x, pair[k - base].y, acc);
+  }
+  if (t >= n) return;
   if (tgt_pos) acc /= (double)tgt_pos[t].w;
-  near_out[t] += acc;
+  out[t] = acc;
 }
 
 struct P2PArgs {
@@ -1374,6 +1394,7 @@ struct P2PArgs {
   double *y;
   double *dbg_near, *dbg_far;  // sorted order, may be NULL
   double *near_out;            // near field per target, sorted order ([n] or [4n]) per part
+  const double *nq_out;        // near quadrature per target, sorted order, or NULL
   const int2 *near_cnt;        // sources of each leaf's near leaves (panels, charges)
   int nseg;                    // parts of the near field
   int nsum;                    // parts that the combine adds
@@ -1902,6 +1923,7 @@ __global__ void __launch_bounds__(64) k_l2p_combine(P2PArgs a) {
       for (int k = 0; k < NC; ++k) nv[k] += no[k];
   }
   near_v = nv[0];
+  if (NC == 1 && a.nq_out) near_v += a.nq_out[ti];
   if (OUT == OUT_POT) {
     far_v = (double)fp;
     res[0] = near_v + far_v;
@@ -2206,6 +2228,9 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   if (!f64 && a.nseg > 1) B.leaf_out.reserve((size_t)nchunks * T.near_max * near_ncomp(rq.out) * 64);
   a.leaf_out = B.leaf_out.p;
   a.near_out = rq.far_only ? nullptr : B.near_out.p;
+  const bool nq = !rq.far_only && nchunks > 0 && T.n_nq > 0 && (rq.op == BEMFMM_OP_A || rq.op == BEMFMM_OP_AT);
+  if (nq) B.nq_out.reserve(T.N);
+  a.nq_out = nq ? B.nq_out.p : nullptr;
   B.last_tgt = rq.tgt;
   // The near field runs on the second stream, forked from the caller's
   // stream at a point of the upward pass and joined before L2P.  In FP32 and
@@ -2267,13 +2292,6 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
       }
 #undef P2P_CALL
       LAUNCH_OK();
-      if (T.n_nq > 0 && (rq.op == BEMFMM_OP_A || rq.op == BEMFMM_OP_AT)) {
-        const bool tr = rq.op == BEMFMM_OP_AT;
-        k_nq_apply<R><<<cdiv(T.N, 256), 256, 0, ss>>>(
-            T.N, tr ? T.nqT_ptr.p : T.nq_ptr.p, tr ? T.nqT_idx.p : T.nq_idx.p, tr ? T.nqT_coef.p : T.nq_coef.p,
-            tr ? rq.wdip : rq.wmono, tr ? reinterpret_cast<const R4 *>(a.tgt_pos) : nullptr, B.near_out.p);
-        LAUNCH_OK();
-      }
       prof_end(T, ST_P2P, ss);
       if (ss != s) HIP_OK(hipEventRecord(T.ev_join, ss));
     }
@@ -2282,6 +2300,17 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
     fork_point();
     launch_near();
   };
+  // the near quadrature needs the product's input only: it goes first on the
+  // second stream
+  if (a.nq_out) {
+    const bool tr = rq.op == BEMFMM_OP_AT;
+    fork_point();
+    if (ss != s) HIP_OK(hipStreamWaitEvent(ss, T.ev_fork, 0));
+    k_nq_apply<R><<<cdiv(T.N, 256), 256, 0, ss>>>(
+        T.N, tr ? T.nqT_ptr.p : T.nq_ptr.p, tr ? T.nqT_idx.p : T.nq_idx.p, tr ? T.nqT_coef.p : T.nq_coef.p,
+        tr ? rq.wdip : rq.wmono, tr ? reinterpret_cast<const R4 *>(a.tgt_pos) : nullptr, B.nq_out.p);
+    LAUNCH_OK();
+  }
   if (fork_at == FORK_START) fork_near();
 
   if (far) {
