@@ -561,8 +561,10 @@ k_level(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile
 // unit instead of RT x 4 x NT).  RT = 2 keeps the accumulators, the
 // prefetched rows and the staging within 256 registers.  The arithmetic per
 // row is that of k_m2l (same operand layouts, same K order), so results are
-// identical.
-template <int NT, int RT>
+// identical.  RB > 0: result rows hold the 4 RB coefficients in packed order
+// without the padding places, as those of the split-bf16 M2L, 11% fewer bytes
+// to write and to read back; RB = 0: the stored layout.
+template <int NT, int RT, int RB>
 __device__ __forceinline__ void m2l_tiles(const int32_t *__restrict__ tile_group,
                                           const int32_t *__restrict__ tile_row,
                                           const int32_t *__restrict__ group_off,
@@ -576,8 +578,9 @@ __device__ __forceinline__ void m2l_tiles(const int32_t *__restrict__ tile_group
   constexpr int UROWS = 4 * RT * 16;         // rows per unit
   static_assert(M2L_ROWS32 % UROWS == 0, "a tile splits into whole units");
   constexpr int SUB = M2L_ROWS32 / UROWS;    // units per tile
-  constexpr int TS = PS + 4;                 // staging row stride (floats, 16-byte aligned)
-  constexpr int F4 = PS / 4;                 // float4 per result row
+  constexpr int CS = RB > 0 ? 4 * RB : PS;   // floats per result row
+  constexpr int TS = CS + 4;                 // staging row stride (floats, 16-byte aligned)
+  constexpr int F4 = CS / 4;                 // float4 per result row
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int i16 = lane & 15, kq = lane >> 4;
   const int nwg = gridDim.x;
@@ -664,20 +667,31 @@ __device__ __forceinline__ void m2l_tiles(const int32_t *__restrict__ tile_group
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         // MFMA output: register q of lane (i16, kq) is row 4 kq + q, column
-        // ct * 16 + i16 of column tile ct
+        // ct * 16 + i16 of column tile ct; in a compact row it goes to its
+        // packed index (the lane index is passed through an empty asm so that
+        // the places are computed here, not held in registers)
+        int il = i16;
+        __asm__ volatile("" : "+v"(il));
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int ct = 0; ct < NT; ++ct) {
+          const int pl = ct * 16 + il, blk = pl / KK, o = pl - blk * KK;
+          const int at = RB > 0 ? 4 * o + blk : pl;
+          if (RB == 0 || o < RB) {
 #pragma unroll
-          for (int ct = 0; ct < NT; ++ct) Tw[(4 * kq + q) * TS + ct * 16 + i16] = acc[rt][ct][q];
+            for (int q = 0; q < 4; ++q) Tw[(4 * kq + q) * TS + at] = acc[rt][ct][q];
+          }
+        }
         __builtin_amdgcn_wave_barrier();
-        // 16 rows x F4 float4, 64 lanes at a time (16 F4 = 64 NT: whole passes)
+        // 16 rows x F4 float4, 64 lanes at a time
+        constexpr int NPASS = (16 * F4 + 63) / 64;
 #pragma unroll
-        for (int v = 0; v < NT; ++v) {
-          const int f = lane + 64 * v;
+        for (int v = 0; v < NPASS; ++v) {
+          const int f = min(lane + 64 * v, 16 * F4 - 1);
           const int row = f / F4, c4 = f - row * F4;
           const int dr = __shfl(d[rt], row);
           const float4 val = *reinterpret_cast<const float4 *>(Tw + row * TS + 4 * c4);
-          if (cur.row0 + rt * 16 + row < cur.end) *reinterpret_cast<float4 *>(out + (size_t)dr * PS + 4 * c4) = val;
+          if (lane + 64 * v < 16 * F4 && cur.row0 + rt * 16 + row < cur.end)
+            *reinterpret_cast<float4 *>(out + (size_t)dr * CS + 4 * c4) = val;
         }
         __builtin_amdgcn_wave_barrier();
       }
@@ -695,15 +709,15 @@ __device__ __forceinline__ void m2l_tiles(const int32_t *__restrict__ tile_group
   }
 }
 
-template <int NT, int RT>
+template <int NT, int RT, int RB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(NT <= 7 ? 2 : 1)))
 k_m2l_pers(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_row,
            const int32_t *__restrict__ group_off, const int32_t *__restrict__ group_end,
            const int32_t *__restrict__ src, const int32_t *__restrict__ dest, const float *__restrict__ Tsw,
            const float *__restrict__ M, float *__restrict__ out, int ntiles) {
   __shared__ float4 Bs[NT * 4 * NT * 16];
-  __shared__ float Ts[4 * 16 * (NT * 16 + 4)];
-  m2l_tiles<NT, RT>(tile_group, tile_row, group_off, group_end, src, dest, Tsw, M, out, ntiles, Bs, Ts);
+  __shared__ float Ts[4 * 16 * ((RB > 0 ? 4 * RB : NT * 16) + 4)];
+  m2l_tiles<NT, RT, RB>(tile_group, tile_row, group_off, group_end, src, dest, Tsw, M, out, ntiles, Bs, Ts);
 }
 
 // Persistent FP32 M2L on the bf16 matrix cores, for the expansion order with
@@ -2256,8 +2270,14 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   const bool split_m2l =
       !f64 && combo == 0 && T.m2l_persistent && T.m2l_split && T.p == P_FIXED && T.t_m2lbf;
   const bool m2l_first = !f64 || big_m2l;
-  // M2L result rows without the padding places (read so by the downward pass)
-  const bool compact_rows = split_m2l;
+  // M2L result rows without the padding places (read so by the downward pass).
+  // The FP32 MFMA kernel scatters them into its staging area at four times the
+  // lane stride, which costs it more LDS time than the bytes give on short
+  // lists: products with charges at 20,480 to 327,680 panels (at most 7 tiles per
+  // CU) took 2-3% longer, while an M2L of 64 molecules (1.3 million panels) went
+  // from 1.24 to 1.00 ms.
+  const bool compact_rows =
+      split_m2l || (!f64 && T.m2l_persistent && T.p == P_FIXED && ML.ntiles >= 8 * (int64_t)T.n_cu);
   const int fork_at = !far ? FORK_START : T.fork_at >= 0 ? T.fork_at : (m2l_first ? FORK_AFTER_M2M : FORK_AFTER_P2M);
   auto fork_point = [&]() {
     if (!rq.far_only && ss != s) HIP_OK(hipEventRecord(T.ev_fork, s));
@@ -2348,7 +2368,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
           ML.tile_group64.p, ML.tile_row64.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l64,             \
           reinterpret_cast<const double *>(M), reinterpret_cast<double *>(m2l));                               \
     else if (T.m2l_persistent)                                                                                  \
-      k_m2l_pers<nt, M2L_PERS_RT><<<dim3((unsigned)std::min<int64_t>(ML.ntiles * (M2L_ROWS32 / (64 * M2L_PERS_RT)), \
+      k_m2l_pers<nt, M2L_PERS_RT, 0><<<dim3((unsigned)std::min<int64_t>(ML.ntiles * (M2L_ROWS32 / (64 * M2L_PERS_RT)), \
                                                                    2 * T.n_cu)), 256, 0, s>>>(                 \
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l32,      \
           reinterpret_cast<const float *>(M), reinterpret_cast<float *>(m2l), (int)ML.ntiles);                 \
@@ -2363,6 +2383,11 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
                 ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p,
                 reinterpret_cast<const bf16x8 *>(T.t_m2lbf), reinterpret_cast<const float *>(M),
                 reinterpret_cast<float *>(m2l), (int)ML.ntiles);
+      } else if (compact_rows) {
+        k_m2l_pers<NT_FIXED, M2L_PERS_RT, RB_FIXED>
+            <<<dim3((unsigned)std::min<int64_t>(ML.ntiles * (M2L_ROWS32 / (64 * M2L_PERS_RT)), 2 * T.n_cu)), 256, 0, s>>>(
+                ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l32,
+                reinterpret_cast<const float *>(M), reinterpret_cast<float *>(m2l), (int)ML.ntiles);
       } else switch (NT) {
         M2L_CASE(1)
         M2L_CASE(2)
