@@ -1726,32 +1726,26 @@ __global__ void __launch_bounds__(64) k_p2p_parts(P2PArgs a) {
         const R r2 = dot3<R>(dx, dy, dz, dx, dy, dz);
         pair_eval_r2<R, SRC, OUT>(s4, m4, dx, dy, dz, r2, skip, lp, lx, ly, lz);
       };
-      if (self) {
-        // K'_ii = 0: the self panel is skipped by index
-        for (int j = sb; j < se; ++j) eval(uniform_load(spos + j), DIPS ? uniform_load(sdip + j) : R4{}, j == ti);
-      } else {
-        auto request = [&](int j, R4(&s4)[PF], R4(&m4)[PF]) {
+      auto request = [&](int j, R4(&s4)[PF], R4(&m4)[PF]) {
 #pragma unroll
-          for (int u = 0; u < PF; ++u) {
-            s4[u] = uniform_load(spos + j + u);
-            if (DIPS) m4[u] = uniform_load(sdip + j + u);
-          }
-          __builtin_amdgcn_sched_barrier(0);  // requested before what follows
-        };
-        // scalar loads return in any order, so a wait for one is a wait for
-        // all: the records at hand are waited for before the next are requested
-        auto arrived = [&](const R4(&s4)[PF], const R4(&m4)[PF]) {
-          __asm__ volatile("" ::"s"(s4[0].x));
-          if (DIPS) __asm__ volatile("" ::"s"(m4[0].x));
-        };
-        auto eval_all = [&](const R4(&s4)[PF], const R4(&m4)[PF]) {
+        for (int u = 0; u < PF; ++u) {
+          s4[u] = uniform_load(spos + j + u);
+          if (DIPS) m4[u] = uniform_load(sdip + j + u);
+        }
+        __builtin_amdgcn_sched_barrier(0);  // requested before what follows
+      };
+      // scalar loads return in any order, so a wait for one is a wait for
+      // all: the records at hand are waited for before the next are requested
+      auto arrived = [&](const R4(&s4)[PF], const R4(&m4)[PF]) {
+        __asm__ volatile("" ::"s"(s4[0].x));
+        if (DIPS) __asm__ volatile("" ::"s"(m4[0].x));
+      };
+      // K'_ii = 0: in the targets' own leaf the self panel is skipped by index
+      auto sweep = [&](auto SELF) {
+        auto eval_n = [&](const R4(&s4)[PF], const R4(&m4)[PF], int j, int n) {
 #pragma unroll
-          for (int u = 0; u < PF; ++u) eval(s4[u], m4[u], false);
-        };
-        auto eval_some = [&](const R4(&s4)[PF], const R4(&m4)[PF], int n) {
-#pragma unroll
-          for (int u = 0; u < PF - 1; ++u)
-            if (u < n) eval(s4[u], m4[u], false);
+          for (int u = 0; u < PF; ++u)
+            if (u < n) eval(s4[u], m4[u], decltype(SELF)::value && j + u == ti);
         };
         // two sets of PF records in turn; past the end of the leaf they are
         // the next leaf's (the arrays are padded) and are not used
@@ -1762,19 +1756,29 @@ __global__ void __launch_bounds__(64) k_p2p_parts(P2PArgs a) {
         for (; q + 2 <= full; q += 2, j += 2 * PF) {
           arrived(as, am);
           request(j + PF, bs, bm);
-          eval_all(as, am);
+          eval_n(as, am, j, PF);
           arrived(bs, bm);
           request(j + 2 * PF, as, am);
-          eval_all(bs, bm);
+          eval_n(bs, bm, j + PF, PF);
         }
         if (q < full) {
           arrived(as, am);
           request(j + PF, bs, bm);
-          eval_all(as, am);
-          eval_some(bs, bm, rest);
+          eval_n(as, am, j, PF);
+          eval_n(bs, bm, j + PF, rest);
         } else {
-          eval_some(as, am, rest);
+          eval_n(as, am, j, rest);
         }
+      };
+      if (!self) {
+        sweep(std::false_type());
+      } else if constexpr (F32 && !DIPS) {
+        // (one at a time the leaf's records made this wave the last of its
+        // chunk: FP32 A at 1,280 and 5,780 panels 31.4 and 74.6 -> 24.5 and 73.0 us;
+        // the others have no scalar registers left for a second sweep)
+        sweep(std::true_type());
+      } else {
+        for (int j = sb; j < se; ++j) eval(uniform_load(spos + j), DIPS ? uniform_load(sdip + j) : R4{}, j == ti);
       }
     } else {
       // several lane groups: the source leaf is staged in LDS, 64 records at
@@ -1843,10 +1847,10 @@ __global__ void __launch_bounds__(64) k_p2p_parts(P2PArgs a) {
 // FP32 near field of several parts: one wave per chunk takes the leaf totals
 // of its lanes, in list order, through the compensated sum of k_p2p_near.
 // Empty leaves have no total.  Bound by the latency of its loads, which are
-// issued 8 leaves at a time.
+// issued 16 leaves at a time.
 template <int SRC, int OUT>
 __global__ void __launch_bounds__(64) k_near_sum(P2PArgs a) {
-  constexpr int NC = near_ncomp(OUT), U = 8;
+  constexpr int NC = near_ncomp(OUT), U = 16;
   __shared__ float red[4][64];
   const int ci = blockIdx.x;
   const int4 ch = a.chunks[ci];
