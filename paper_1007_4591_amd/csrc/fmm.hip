@@ -2238,12 +2238,16 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   B.dbg_valid = T.debug_record;
   a.near_cnt = T.near_cnt.p;
   a.nseg = rq.far_only ? 1 : near_parts(T, src_charges, tgt_ch, nchunks, near_ncomp(rq.out));
+  // leaf totals of FP32 parts: 0.1 GB at 81,920 panels; the near lists of a small
+  // theta are longer, and beyond 1 GB the chunks stay whole
+  const size_t leaf_reals = (size_t)nchunks * T.near_max * near_ncomp(rq.out) * 64;
+  if (!f64 && leaf_reals > ((size_t)1 << 28)) a.nseg = 1;
   a.nsum = f64 ? a.nseg : 1;
   const int64_t ntgt = tgt_ch ? T.Q : T.N;
   a.seg_stride = (size_t)ntgt * (rq.out == OUT_POTGRAD ? 4 : 1);
   if (!rq.far_only) B.near_out.reserve(a.nsum * a.seg_stride);
   a.near_max = T.near_max;
-  if (!f64 && a.nseg > 1) B.leaf_out.reserve((size_t)nchunks * T.near_max * near_ncomp(rq.out) * 64);
+  if (!f64 && a.nseg > 1) B.leaf_out.reserve(leaf_reals);
   a.leaf_out = B.leaf_out.p;
   a.near_out = rq.far_only ? nullptr : B.near_out.p;
   const bool nq = !rq.far_only && nchunks > 0 && T.n_nq > 0 && (rq.op == BEMFMM_OP_A || rq.op == BEMFMM_OP_AT);
