@@ -57,9 +57,13 @@
  *   product, after P2M, after M2M or after M2L (default: after M2M when the
  *   M2L has at least 32 tiles of 256 pairs per compute unit, or 8 for the
  *   split-bf16 FP32 M2L, else after P2M);
+ *   BEMFMM_NEAR_PARTS=1..32 splits the sources of every near field into so
+ *   many parts (1: none; default: by the number of targets and the length of
+ *   the near lists);
  *   BEMFMM_CACHE_LIMIT_MB caps the device memory kept for reuse per device
  *   (default: half of the device's memory, see bemfmm_release_cache).
- *   Results do not depend on BEMFMM_CONCURRENT_P2P or BEMFMM_FORK_AT.  The
+ *   Results do not depend on BEMFMM_CONCURRENT_P2P or BEMFMM_FORK_AT, and in
+ *   FP32 not on BEMFMM_NEAR_PARTS (in FP64 to rounding).  The
  *   split-bf16 M2L (the default for FP32 A and A^T at order 10) and the FP32
  *   ones selected by the two M2L switches agree to FP32 rounding; the FP32
  *   ones agree with each other bitwise.

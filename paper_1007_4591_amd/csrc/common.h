@@ -339,6 +339,7 @@ struct Tree {
   bool m2l_persistent = true;    // FP32 M2L: persistent workgroups (else one tile per workgroup)
   bool m2l_split = true;         // persistent FP32 M2L of order P_FIXED on split-bf16 MFMA (else FP32 MFMA)
   int fork_at = -1;              // where the near field forks: a ForkAt value, -1 = per precision
+  int near_parts = 0;            // parts of every near field (1: whole chunks), 0 = by rule
   int n_cu = 256;                // compute units of the device
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   bool prof = false;

@@ -2085,7 +2085,9 @@ static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
 int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, int sums) {
   constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32;
   const int64_t simds = 4 * (int64_t)T.n_cu;
-  if (nchunks <= 0 || (sums > 1 && nchunks > 4 * simds)) return 1;
+  if (nchunks <= 0) return 1;
+  if (T.near_parts > 0) return T.near_parts;
+  if (sums > 1 && nchunks > 4 * simds) return 1;
   const int64_t npts = std::max<int64_t>(tgt_charges ? T.Q : T.N, 1);
   const int64_t mean = T.near_pairs[src_charges][tgt_charges] / npts;  // sources per target
   const int64_t want = cdiv(WAVES_PER_SIMD * simds, nchunks);
@@ -2479,6 +2481,7 @@ void fmm_init(Tree &T) {
   // the split-bf16 M2L takes more dynamic LDS than the default limit
   HIP_OK(hipFuncSetAttribute((const void *)k_m2l_bf<NT_FIXED, RB_FIXED>, hipFuncAttributeMaxDynamicSharedMemorySize,
                              M2L_BF_LDS));
+  if (const char *e = getenv("BEMFMM_NEAR_PARTS")) T.near_parts = std::min(std::max(atoi(e), 0), 32);
   if (const char *e = getenv("BEMFMM_FORK_AT")) T.fork_at = std::min(std::max(atoi(e), -1), (int)FORK_AFTER_M2L);
   int dev = 0;
   HIP_OK(hipGetDevice(&dev));
