@@ -1412,7 +1412,7 @@ struct P2PArgs {
   const int2 *near_cnt;        // sources of each leaf's near leaves (panels, charges)
   int nseg;                    // parts of the near field
   int nsum;                    // parts that the combine adds
-  size_t seg_stride;           // reals of near_out per part
+  size_t seg_stride;           // reals of near_out per part: the sums, then (several parts) their rests
   float *leaf_out;             // FP32, several parts: leaf totals [chunk][near_max][components][64 lanes]
   int near_max;                // longest near list
 };
@@ -1621,15 +1621,24 @@ __device__ __forceinline__ T4 uniform_load(const T4 *p) {
 // The near field in parts: one wave per task, a chunk against one of `nseg`
 // parts of the sources of its near leaves, counted in list order.  Lanes,
 // lane groups and the sum over a leaf are those of k_p2p_near.  In FP64 the
-// parts are equal, and the combine adds their results (near_out[part]) in
-// order.  In FP32 they are whole leaves, and the leaf totals of every lane go
-// to leaf_out; k_near_sum takes them through the compensated sum of k_p2p_near
-// in its order, so that the bits do not depend on the split.
+// parts are equal, and each stores its compensated sum with the rest that one
+// FP64 number does not hold (near_out[part]); the combine adds both, so the
+// split costs no digits.  In FP32 they are whole leaves, and the leaf totals of
+// every lane go to leaf_out; k_near_sum takes them through the compensated sum
+// of k_p2p_near in its order, so that the bits do not depend on the split.
 // These waves are few, and wait for their loads: the near list is read 64
 // leaves at a time (near_batch), and PF records are requested before the PF at
 // hand are evaluated.  With every SIMD full k_p2p_near's loop, whose wait the
 // other waves cover, is the faster (FP32 A, 10.5 million panels, near field in
 // line: 39.5 against 41.8 ms per product).
+// s + v: the rounded sum stays in s, its rounding error is added to e
+__device__ __forceinline__ void two_sum(double &s, double &e, double v) {
+#pragma clang fp contract(off)
+  const double t = s + v, b = t - s;
+  e += (s - (t - b)) + (v - b);
+  s = t;
+}
+
 template <class R, int OUT>
 struct NearAcc {
   // compensated sums of the potential and of the three gradient components
@@ -1644,9 +1653,15 @@ struct NearAcc {
       s[k] = t;
     }
   }
-  // adds the G lane groups in group order and stores the target's result
+  // Adds the G lane groups in group order and stores the target's result; in
+  // FP64 the sum is s - c, and what a single number drops of it goes to
+  // near_out[lo + ...].  (Where 500 to 650 terms cancel, parts that kept s alone,
+  // added plainly, were up to 606 roundings of the largest term off one
+  // compensated sum over all of them; with the rests 23.)
   __device__ __forceinline__ void finish(R (*red)[64], int G, int count, int g, int tl, int ti, const void *tgt_nrm,
-                                         double *near_out) {
+                                         double *near_out, size_t lo) {
+#pragma clang fp contract(off)
+    constexpr bool F64 = std::is_same<R, double>::value;
     if (G > 1) {
       __syncthreads();  // the last staged records are no longer read
 #pragma unroll
@@ -1656,16 +1671,48 @@ struct NearAcc {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
           s[k] = red[k][tl];
-          c[k] = R(0);
+          if (!F64) c[k] = R(0);
         }
         for (int h = 1; h < G; ++h) {
           const int o = h * count + tl;
           add(red[0][o], red[1][o], red[2][o], red[3][o]);
         }
       }
+      if constexpr (F64) {
+        const R own[4] = {c[0], c[1], c[2], c[3]};
+        __syncthreads();  // the groups' sums are no longer read
+#pragma unroll
+        for (int k = 0; k < 4; ++k) red[k][threadIdx.x] = own[k];
+        __syncthreads();
+        if (g == 0)
+          for (int h = 1; h < G; ++h) {
+            const int o = h * count + tl;
+            add(-red[0][o], -red[1][o], -red[2][o], -red[3][o]);
+          }
+      }
     }
     if (g != 0) return;
-    if (OUT == OUT_POT) {
+    if constexpr (F64) {
+      if (OUT == OUT_NGRAD) {
+        // n . (s - c): products and sums with their rounding errors
+        const double4 nn = reinterpret_cast<const double4 *>(tgt_nrm)[ti];
+        const double px = nn.x * s[1], py = nn.y * s[2], pz = nn.z * s[3];
+        double e = fma_(nn.x, s[1], -px) + fma_(nn.y, s[2], -py) + fma_(nn.z, s[3], -pz);
+        double t = px;
+        two_sum(t, e, py);
+        two_sum(t, e, pz);
+        e -= nn.x * c[1] + nn.y * c[2] + nn.z * c[3];
+        near_out[ti] = -t;
+        near_out[lo + ti] = -e;
+      } else {
+        constexpr int NC = OUT == OUT_POT ? 1 : 4;
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          near_out[NC * (size_t)ti + k] = k == 0 ? s[k] : -s[k];
+          near_out[lo + NC * (size_t)ti + k] = k == 0 ? -c[k] : c[k];
+        }
+      }
+    } else if (OUT == OUT_POT) {
       near_out[ti] = (double)s[0];
     } else if (OUT == OUT_NGRAD) {
       const typename V4<R>::T nn = reinterpret_cast<const typename V4<R>::T *>(tgt_nrm)[ti];
@@ -1841,7 +1888,7 @@ __global__ void __launch_bounds__(64) k_p2p_parts(P2PArgs a) {
   }
   if constexpr (F32) return;
   acc.finish(reinterpret_cast<R(*)[64]>(src_s), G, count, g, tl, ti, a.tgt_nrm,
-             a.near_out + (size_t)seg * a.seg_stride);
+             a.near_out + (size_t)seg * a.seg_stride, a.seg_stride / 2);
 }
 
 // FP32 near field of several parts: one wave per chunk takes the leaf totals
@@ -1879,7 +1926,7 @@ __global__ void __launch_bounds__(64) k_near_sum(P2PArgs a) {
         if (full >> (i + u) & 1) acc.add(v[u][0], v[u][1], v[u][2], v[u][3]);
     }
   }
-  acc.finish(red, G, count, g, tl, ch.y + tl, a.tgt_nrm, a.near_out);
+  acc.finish(red, G, count, g, tl, ch.y + tl, a.tgt_nrm, a.near_out, 0);
 }
 
 // Far field (L2P from the leaf's evaluation coefficients, read through the
@@ -1935,10 +1982,21 @@ __global__ void __launch_bounds__(64) k_l2p_combine(P2PArgs a) {
   double nv[NC] = {};
   if (a.near_out) {
     const double *no = a.near_out + NC * (size_t)ti;
-#pragma unroll 8
-    for (int q = 0; q < a.nsum; ++q, no += a.seg_stride)
+    if (sizeof(R) == 4 || a.nsum == 1) {
 #pragma unroll
-      for (int k = 0; k < NC; ++k) nv[k] += no[k];
+      for (int k = 0; k < NC; ++k) nv[k] = no[k];
+    } else {
+      double e[NC] = {};
+#pragma unroll 8
+      for (int q = 0; q < a.nsum; ++q, no += a.seg_stride)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          two_sum(nv[k], e[k], no[k]);
+          e[k] += no[a.seg_stride / 2 + k];
+        }
+#pragma unroll
+      for (int k = 0; k < NC; ++k) nv[k] += e[k];
+    }
   }
   near_v = nv[0];
   if (NC == 1 && a.nq_out) near_v += a.nq_out[ti];
@@ -2246,7 +2304,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   if (!f64 && leaf_reals > ((size_t)1 << 28)) a.nseg = 1;
   a.nsum = f64 ? a.nseg : 1;
   const int64_t ntgt = tgt_ch ? T.Q : T.N;
-  a.seg_stride = (size_t)ntgt * (rq.out == OUT_POTGRAD ? 4 : 1);
+  a.seg_stride = (size_t)ntgt * (rq.out == OUT_POTGRAD ? 4 : 1) * (a.nsum > 1 ? 2 : 1);
   if (!rq.far_only) B.near_out.reserve(a.nsum * a.seg_stride);
   a.near_max = T.near_max;
   if (!f64 && a.nseg > 1) B.leaf_out.reserve(leaf_reals);
