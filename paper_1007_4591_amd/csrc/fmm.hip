@@ -2099,30 +2099,6 @@ static void prof_collect(Tree &T) {
   }
 }
 
-static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
-  PrecBufs *&pb = (prec == BEMFMM_FP64) ? T.pb64 : T.pb32;
-  if (!pb) {
-    pb = new PrecBufs();
-    const size_t rs = (prec == BEMFMM_FP64) ? 8 : 4;
-    const int64_t npts = std::max<int64_t>(std::max(T.N, T.Q), 1);
-    // the near field reads up to 8 records past a leaf's sources
-    pb->src_pos.alloc((npts + 8) * 4 * rs);
-    pb->src_dip.alloc((npts + 8) * 4 * rs);
-    pb->M.alloc((size_t)T.ncell_tot * T.ps * rs);
-    pb->L.alloc((size_t)T.ncell_tot * T.ps * rs);
-    pb->m2l_out.alloc((size_t)std::max<int64_t>(T.nfar, 1) * T.ps * rs);
-    pb->l2l_out.alloc((size_t)std::max<int64_t>(T.l2lw.max_cells, 1) * T.ps * rs);
-    pb->E.alloc((size_t)T.ncell[T.L] * 4 * T.ps * rs);
-    pb->near_out.alloc(4 * npts);
-    pb->M.zero(s);
-    pb->L.zero(s);
-    pb->E.zero(s);
-    pb->src_dip.zero(s);
-    pb->prec = prec;
-  }
-  return *pb;
-}
-
 // Parts the near field of a target chunk is split into.  A wave alone on its
 // SIMD takes about 150 clocks per source (64 pairs), eight waves together
 // about 43, and waves of unequal length leave SIMDs idle at the end.  Chunks
@@ -2150,6 +2126,66 @@ int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunk
   const int64_t mean = T.near_pairs[src_charges][tgt_charges] / npts;  // sources per target
   const int64_t want = cdiv(WAVES_PER_SIMD * simds, nchunks);
   return (int)std::max<int64_t>(1, std::min(std::min(want, mean / MIN_SOURCES), MAX_PARTS));
+}
+
+// The near field's split of a product and its scratch: reals of near_out (a sum
+// per target and part, and with several parts the rests), floats of leaf_out.
+struct NearPlan {
+  int nseg;         // parts of a chunk, one wave each
+  int nsum;         // results per target that the combine adds
+  size_t stride;    // reals of near_out per result
+  size_t leaf;
+};
+
+static NearPlan near_plan(const Tree &T, bool f64, bool src_charges, bool tgt_charges, int out) {
+  const int64_t nchunks = tgt_charges ? T.nchunk_q : T.nchunk_p, ntgt = tgt_charges ? T.Q : T.N;
+  const int nc = near_ncomp(out);
+  NearPlan P;
+  P.nseg = near_parts(T, src_charges, tgt_charges, nchunks, nc);
+  // leaf totals of FP32 parts: 0.1 GB at 81,920 panels; the near lists of a small
+  // theta are longer, and beyond 1 GB the chunks stay whole
+  P.leaf = (size_t)nchunks * T.near_max * nc * 64;
+  if (!f64 && P.leaf > ((size_t)1 << 28)) P.nseg = 1;
+  if (f64 || P.nseg == 1) P.leaf = 0;
+  P.nsum = f64 ? P.nseg : 1;
+  P.stride = (size_t)ntgt * (out == OUT_POTGRAD ? 4 : 1) * (P.nsum > 1 ? 2 : 1);
+  return P;
+}
+
+static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
+  PrecBufs *&pb = (prec == BEMFMM_FP64) ? T.pb64 : T.pb32;
+  if (!pb) {
+    pb = new PrecBufs();
+    const size_t rs = (prec == BEMFMM_FP64) ? 8 : 4;
+    const int64_t npts = std::max<int64_t>(std::max(T.N, T.Q), 1);
+    // the near field reads up to 8 records past a leaf's sources
+    pb->src_pos.alloc((npts + 8) * 4 * rs);
+    pb->src_dip.alloc((npts + 8) * 4 * rs);
+    pb->M.alloc((size_t)T.ncell_tot * T.ps * rs);
+    pb->L.alloc((size_t)T.ncell_tot * T.ps * rs);
+    pb->m2l_out.alloc((size_t)std::max<int64_t>(T.nfar, 1) * T.ps * rs);
+    pb->l2l_out.alloc((size_t)std::max<int64_t>(T.l2lw.max_cells, 1) * T.ps * rs);
+    pb->E.alloc((size_t)T.ncell[T.L] * 4 * T.ps * rs);
+    // for every kind of product, so that none after the first allocates: a product may
+    // be captured into a graph, which keeps the addresses
+    size_t near = 4 * npts, leaf = 0;
+    const int kinds[6][3] = {{0, 0, OUT_NGRAD}, {0, 0, OUT_POT}, {1, 0, OUT_NGRAD},
+                             {1, 0, OUT_POT},   {0, 1, OUT_POT}, {0, 1, OUT_POTGRAD}};
+    for (const auto &k : kinds) {
+      const NearPlan P = near_plan(T, prec == BEMFMM_FP64, k[0], k[1], k[2]);
+      near = std::max(near, P.nsum * P.stride);
+      leaf = std::max(leaf, P.leaf);
+    }
+    pb->near_out.alloc(near);
+    pb->leaf_out.alloc(leaf);
+    if (T.n_nq > 0) pb->nq_out.alloc(T.N);
+    pb->M.zero(s);
+    pb->L.zero(s);
+    pb->E.zero(s);
+    pb->src_dip.zero(s);
+    pb->prec = prec;
+  }
+  return *pb;
 }
 
 template <class R>
@@ -2297,21 +2333,17 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   a.dbg_far = T.debug_record ? B.dbg_far.p : nullptr;
   B.dbg_valid = T.debug_record;
   a.near_cnt = T.near_cnt.p;
-  a.nseg = rq.far_only ? 1 : near_parts(T, src_charges, tgt_ch, nchunks, near_ncomp(rq.out));
-  // leaf totals of FP32 parts: 0.1 GB at 81,920 panels; the near lists of a small
-  // theta are longer, and beyond 1 GB the chunks stay whole
-  const size_t leaf_reals = (size_t)nchunks * T.near_max * near_ncomp(rq.out) * 64;
-  if (!f64 && leaf_reals > ((size_t)1 << 28)) a.nseg = 1;
-  a.nsum = f64 ? a.nseg : 1;
-  const int64_t ntgt = tgt_ch ? T.Q : T.N;
-  a.seg_stride = (size_t)ntgt * (rq.out == OUT_POTGRAD ? 4 : 1) * (a.nsum > 1 ? 2 : 1);
-  if (!rq.far_only) B.near_out.reserve(a.nsum * a.seg_stride);
+  if (!rq.far_only) {
+    const NearPlan P = near_plan(T, f64, src_charges, tgt_ch, rq.out);
+    if (P.nsum * P.stride > B.near_out.n || P.leaf > B.leaf_out.n) BF_THROW(BEMFMM_EINVAL, "unsupported FMM request");
+    a.nseg = P.nseg;
+    a.nsum = P.nsum;
+    a.seg_stride = P.stride;
+  }
   a.near_max = T.near_max;
-  if (!f64 && a.nseg > 1) B.leaf_out.reserve(leaf_reals);
   a.leaf_out = B.leaf_out.p;
   a.near_out = rq.far_only ? nullptr : B.near_out.p;
   const bool nq = !rq.far_only && nchunks > 0 && T.n_nq > 0 && (rq.op == BEMFMM_OP_A || rq.op == BEMFMM_OP_AT);
-  if (nq) B.nq_out.reserve(T.N);
   a.nq_out = nq ? B.nq_out.p : nullptr;
   B.last_tgt = rq.tgt;
   // The near field runs on the second stream, forked from the caller's
