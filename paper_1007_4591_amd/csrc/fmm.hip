@@ -2153,9 +2153,10 @@ static NearPlan near_plan(const Tree &T, bool f64, bool src_charges, bool tgt_ch
 }
 
 static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
-  PrecBufs *&pb = (prec == BEMFMM_FP64) ? T.pb64 : T.pb32;
-  if (!pb) {
-    pb = new PrecBufs();
+  PrecBufs *&have = (prec == BEMFMM_FP64) ? T.pb64 : T.pb32;
+  if (!have) {
+    // the tree's once they are complete: an allocation that fails leaves none behind
+    std::unique_ptr<PrecBufs> pb(new PrecBufs());
     const size_t rs = (prec == BEMFMM_FP64) ? 8 : 4;
     const int64_t npts = std::max<int64_t>(std::max(T.N, T.Q), 1);
     // the near field reads up to 8 records past a leaf's sources
@@ -2184,8 +2185,9 @@ static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
     pb->E.zero(s);
     pb->src_dip.zero(s);
     pb->prec = prec;
+    have = pb.release();
   }
-  return *pb;
+  return *have;
 }
 
 template <class R>
