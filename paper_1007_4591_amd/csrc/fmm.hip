@@ -48,6 +48,7 @@ struct PrecBufs {
   DBuf<double> nq_out;             // near quadrature per target (sorted order)
   DBuf<float> leaf_out;            // FP32 near field of several parts: leaf totals per lane
   int last_tgt = 0;
+  bool whole = false;              // no memory for the near field in parts: whole chunks
   bool have = false;
 };
 
@@ -2137,11 +2138,11 @@ struct NearPlan {
   size_t leaf;
 };
 
-static NearPlan near_plan(const Tree &T, bool f64, bool src_charges, bool tgt_charges, int out) {
+static NearPlan near_plan(const Tree &T, bool f64, bool whole, bool src_charges, bool tgt_charges, int out) {
   const int64_t nchunks = tgt_charges ? T.nchunk_q : T.nchunk_p, ntgt = tgt_charges ? T.Q : T.N;
   const int nc = near_ncomp(out);
   NearPlan P;
-  P.nseg = near_parts(T, src_charges, tgt_charges, nchunks, nc);
+  P.nseg = whole ? 1 : near_parts(T, src_charges, tgt_charges, nchunks, nc);
   // leaf totals of FP32 parts: 0.1 GB at 81,920 panels; the near lists of a small
   // theta are longer, and beyond 1 GB the chunks stay whole
   P.leaf = (size_t)nchunks * T.near_max * nc * 64;
@@ -2167,19 +2168,26 @@ static PrecBufs &bufs(Tree &T, int prec, hipStream_t s) {
     pb->m2l_out.alloc((size_t)std::max<int64_t>(T.nfar, 1) * T.ps * rs);
     pb->l2l_out.alloc((size_t)std::max<int64_t>(T.l2lw.max_cells, 1) * T.ps * rs);
     pb->E.alloc((size_t)T.ncell[T.L] * 4 * T.ps * rs);
+    if (T.n_nq > 0) pb->nq_out.alloc(T.N);
     // for every kind of product, so that none after the first allocates: a product may
-    // be captured into a graph, which keeps the addresses
+    // be captured into a graph, which keeps the addresses.  The parts' scratch is there
+    // for speed only: where it does not fit, chunks stay whole for the tree's life
     size_t near = 4 * npts, leaf = 0;
     const int kinds[6][3] = {{0, 0, OUT_NGRAD}, {0, 0, OUT_POT}, {1, 0, OUT_NGRAD},
                              {1, 0, OUT_POT},   {0, 1, OUT_POT}, {0, 1, OUT_POTGRAD}};
     for (const auto &k : kinds) {
-      const NearPlan P = near_plan(T, prec == BEMFMM_FP64, k[0], k[1], k[2]);
+      const NearPlan P = near_plan(T, prec == BEMFMM_FP64, false, k[0], k[1], k[2]);
       near = std::max(near, P.nsum * P.stride);
       leaf = std::max(leaf, P.leaf);
     }
-    pb->near_out.alloc(near);
-    pb->leaf_out.alloc(leaf);
-    if (T.n_nq > 0) pb->nq_out.alloc(T.N);
+    try {
+      pb->near_out.alloc(near);
+      pb->leaf_out.alloc(leaf);
+    } catch (const Error &e) {
+      if (e.code != BEMFMM_ENOMEM) throw;
+      pb->whole = true;
+      pb->near_out.alloc(4 * npts);
+    }
     pb->M.zero(s);
     pb->L.zero(s);
     pb->E.zero(s);
@@ -2336,7 +2344,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   B.dbg_valid = T.debug_record;
   a.near_cnt = T.near_cnt.p;
   if (!rq.far_only) {
-    const NearPlan P = near_plan(T, f64, src_charges, tgt_ch, rq.out);
+    const NearPlan P = near_plan(T, f64, B.whole, src_charges, tgt_ch, rq.out);
     if (P.nsum * P.stride > B.near_out.n || P.leaf > B.leaf_out.n) BF_THROW(BEMFMM_EINVAL, "unsupported FMM request");
     a.nseg = P.nseg;
     a.nsum = P.nsum;

@@ -73,6 +73,27 @@ def test_product_after_one_that_found_no_memory(prec):
     B.tree_destroy(t)
 
 
+def test_near_field_without_room_for_its_parts():
+    """FP32 leaf totals are scratch that only a near field in parts needs: with
+    room for half of them the product runs whole chunks, to the same bits."""
+    B = lib()
+    p, t = _build(B)
+    x = dev(np.random.default_rng(2).normal(size=p.n_panels))
+    near = np.diff(B.tree_export(t)["near_ptr"]).max()
+    leaf = t.info["n_leaves"] * int(near) * 3 * 64 * 4
+    assert 100 * MB <= leaf <= 1024 * MB
+    want, used = _first_product(B, t, B.FP32, x)
+    B.tree_destroy(t)
+    p, t = _build(B)
+    y = torch_empty(p.n_panels)
+    with Low(used - leaf / 2):
+        got = [host(B.fmm_matvec(t, op, B.FP32, x, y=y)) for op in (B.OP_A, B.OP_AT, B.OP_A)]
+    np.testing.assert_array_equal(got[0], want)
+    np.testing.assert_array_equal(got[2], want)
+    np.testing.assert_array_equal(host(B.fmm_matvec(t, B.OP_AT, B.FP32, x)), got[1])
+    B.tree_destroy(t)
+
+
 def torch_empty(n):
     import torch
     return torch.empty(n, dtype=torch.float64, device="cuda")
