@@ -103,16 +103,25 @@ __global__ void k_axpy(double *__restrict__ y, const double *__restrict__ x, dou
 //   k_arn_orth    h1 = sum p1, w -= V h1, p2 = parts of V^T w
 //   k_arn_orth    h2 = sum p2, w -= V h2, p3 = parts of w.w   (LAST)
 //   k_arn_next    |w|^2 = sum p3, v_(k+1) = w / |w|
-// Separate dots, reductions and updates took nine launches and a scaling after
-// the host had seen the norm.  The steps are bound by launches: at 1,280 rows
-// a FP64 solve took 91 launches and 0.78 ms, now 54 and 0.45 ms.  Above
-// ARN_MAX_ROWS the partials that every workgroup would add outgrow the rows
-// that it owns, and the separate kernels, with one workgroup per vector and
-// part, are kept.
+// Separate dots, reductions and updates take nine launches and a scaling after
+// the host has seen the norm.  With few vectors the steps are bound by launches:
+// at 1,280 rows a FP64 solve took 91 launches and 0.78 ms, now 54 and 0.45 ms.
+// But here a workgroup takes the vectors one after another, while the separate
+// kernels have a workgroup for each vector and part: what the launches save, about
+// 20 us a step, goes at 0.6 us a vector and 0.6 us more per 90,000 rows.  The two
+// are level (separate against fused, us a step with the product) at k = 30 to 45
+// of 1,280 rows (124 : 119 at k = 22, 134 : 145 at 38), 22 of 46,080 (166 : 167),
+// 12 of 162,000 (223 : 219) and 6 of 450,000 (291 : 303), which arn_few follows.
+// FP32 solves, all steps fused, all separate, this rule: 60 steps at 81,920 panels
+// 25.8, 28.5 and 22.5 ms, 30 at 327,680 34.3, 33.3 and 32.5 ms, 100 there 136, 112
+// and 110 ms, 120 at 1,280 19.4, 26.4 and 12.2 ms.
 constexpr int ARN_RPT = 8;                       // rows per thread at most
 constexpr int ARN_MAX_NB = 256;
 constexpr int64_t ARN_MAX_ROWS = (int64_t)ARN_MAX_NB * RB * ARN_RPT;
-constexpr int ARN_MAX_VECS = 1000;               // 40 KB of LDS
+constexpr int64_t ARN_ROWS0 = 90000, ARN_WORK = 2900000;
+constexpr int ARN_MAX_VECS = ARN_WORK / ARN_ROWS0;  // 32: 1.3 KB of LDS
+
+inline bool arn_few(int64_t n, int k) { return n <= ARN_MAX_ROWS && k * (n + ARN_ROWS0) <= ARN_WORK; }
 
 __device__ inline double wave_sum(double v) {
 #pragma unroll
@@ -283,7 +292,7 @@ struct Ws {
     cap = (size_t)std::max(1, std::min(512, (int)((T.N + 4 * 256 - 1) / (4 * 256)))) * std::max<size_t>(nvec, 1);
     const int64_t nmax = std::max<int64_t>(std::max<int64_t>(T.N, T.Q), nlen);
     cap = std::max(cap, (size_t)std::max(1, std::min(512, (int)((nmax + 1023) / 1024))) * std::max<size_t>(nvec, 1));
-    cap = std::max(cap, 2 * std::max<size_t>(nvec, 1) * ARN_MAX_NB);
+    cap = std::max(cap, (size_t)2 * ARN_MAX_VECS * ARN_MAX_NB);
     partial = T.buf(std::string("wsp_") + tag, cap);
     h = T.buf(std::string("wsh_") + tag, 4);
   }
@@ -326,7 +335,6 @@ GmresOut gmres_fn(Tree &T, const std::function<void(const double *, double *)> &
   GmresOut out;
   double beta = bnorm;
   const int TB = 256;
-  const bool few = n <= ARN_MAX_ROWS && m <= ARN_MAX_VECS;
   const int nb = (int)std::min<int64_t>(ARN_MAX_NB, cdiv(n, RB));
   bool have_x = false;  // x holds the sum of the cycles so far (0 before the first)
   auto zero_x = [&]() {
@@ -359,6 +367,7 @@ GmresOut gmres_fn(Tree &T, const std::function<void(const double *, double *)> &
       A(vk, w.p);
       // classical Gram-Schmidt, twice: h1 at hd, h2 and |w|^2 after it
       double *h1d = hd.p, *h2d = hd.p + (k + 1);
+      const bool few = arn_few(n, k + 1);
       if (few) {
         const size_t lds = (size_t)(k + 1) * (1 + RB / 64) * sizeof(double) + RB / 64 * sizeof(double);
         double *p1 = ws.partial, *p2 = p1 + (size_t)(k + 1) * nb;
