@@ -671,27 +671,34 @@ __device__ __forceinline__ void m2l_tiles(const int32_t *__restrict__ tile_group
         // ct * 16 + i16 of column tile ct; in a compact row it goes to its
         // packed index (the lane index is passed through an empty asm so that
         // the places are computed here, not held in registers)
-        int il = i16;
-        __asm__ volatile("" : "+v"(il));
+        if constexpr (RB > 0) {
+          int il = i16;
+          __asm__ volatile("" : "+v"(il));
 #pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-          const int pl = ct * 16 + il, blk = pl / KK, o = pl - blk * KK;
-          const int at = RB > 0 ? 4 * o + blk : pl;
-          if (RB == 0 || o < RB) {
+          for (int ct = 0; ct < NT; ++ct) {
+            const int pl = ct * 16 + il, blk = pl / KK, o = pl - blk * KK;
+            if (o < RB) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) Tw[(4 * kq + q) * TS + at] = acc[rt][ct][q];
+              for (int q = 0; q < 4; ++q) Tw[(4 * kq + q) * TS + 4 * o + blk] = acc[rt][ct][q];
+            }
           }
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int ct = 0; ct < NT; ++ct) Tw[(4 * kq + q) * TS + ct * 16 + i16] = acc[rt][ct][q];
         }
         __builtin_amdgcn_wave_barrier();
-        // 16 rows x F4 float4, 64 lanes at a time
+        // 16 rows x F4 float4, 64 lanes at a time (RB = 0: whole passes)
         constexpr int NPASS = (16 * F4 + 63) / 64;
+        constexpr bool WHOLE = 16 * F4 % 64 == 0;
 #pragma unroll
         for (int v = 0; v < NPASS; ++v) {
-          const int f = min(lane + 64 * v, 16 * F4 - 1);
+          const int f = WHOLE ? lane + 64 * v : min(lane + 64 * v, 16 * F4 - 1);
           const int row = f / F4, c4 = f - row * F4;
           const int dr = __shfl(d[rt], row);
           const float4 val = *reinterpret_cast<const float4 *>(Tw + row * TS + 4 * c4);
-          if (lane + 64 * v < 16 * F4 && cur.row0 + rt * 16 + row < cur.end)
+          if ((WHOLE || lane + 64 * v < 16 * F4) && cur.row0 + rt * 16 + row < cur.end)
             *reinterpret_cast<float4 *>(out + (size_t)dr * CS + 4 * c4) = val;
         }
         __builtin_amdgcn_wave_barrier();
