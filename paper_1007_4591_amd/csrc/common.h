@@ -40,7 +40,7 @@ constexpr int M2L_ROWS32 = 4 * M2L_RT32 * 16, M2L_ROWS64 = 4 * M2L_RT64 * 16;
 // row tiles per wave of the persistent FP32 M2L (a tile list tile is split into
 // units of 4 * M2L_PERS_RT * 16 rows)
 constexpr int M2L_PERS_RT = 2;
-constexpr int LEVEL_ROWS = 64;  // rows of a per-level M2M or L2L tile (four workgroups of 16)
+constexpr int LEVEL_ROWS = 64;  // rows of a per-level M2M or L2L tile (one workgroup, or four of 16)
 constexpr double PI = 3.14159265358979323846;
 constexpr double K_COULOMB = 332.06;
 
@@ -297,7 +297,7 @@ struct Tree {
   // are [t0[l], t1[l]) in both precisions.
   struct L2LList {
     DBuf<int32_t> src, self, dest, group_off, group_end;
-    // tiles of 64 rows, four workgroups of 16 rows each
+    // tiles of 64 rows
     DBuf<int32_t> tile_group, tile_row;
     std::vector<int64_t> t0, t1;
     int64_t max_cells = 0;

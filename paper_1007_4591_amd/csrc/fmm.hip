@@ -373,6 +373,8 @@ __global__ void k_m2m_sum(int ps, int64_t cp0, int64_t CP, int64_t cl0, const in
 // source row: at k-step kk, lane group g = lane/16 supplies input g*KK + kk
 // (the B table is stored in that order).  Rows past the end of the group
 // repeat its last row (MFMA rows are independent; they are not stored).
+// The same kernel runs per-level M2M and L2L products (level_product); USE only
+// names the instance (0: M2L, 1: L2L, 2: M2M) so that profiles tell them apart.
 // Registers are budgeted for two waves per SIMD so that one wave's gather
 // overlaps the other's MFMA work.  With BLDS the four waves of a tile share
 // the operator through LDS instead of each reading it from L2.
@@ -382,7 +384,7 @@ __global__ void k_m2m_sum(int ps, int64_t cp0, int64_t CP, int64_t cl0, const in
 // Output layouts (checked on the device): FP32 16x16x4 puts
 // D[4*(lane/16) + q][lane%16] in register q; FP64 16x16x4 puts
 // D[lane/16 + 4*q][lane%16] in register q.
-template <class R, int NT, int RT, bool BLDS>
+template <class R, int NT, int RT, bool BLDS, int USE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 k_m2l(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_row,
       const int32_t *__restrict__ group_off, const int32_t *__restrict__ group_end, const int32_t *__restrict__ src,
@@ -493,12 +495,14 @@ k_m2l(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_r
 // one wave per 16 rows and all column tiles a product took 20-22 us in FP64 and
 // 9.5 us in FP32 at these sizes, now 7-8.5 and 8 us.  Operand layouts and K order
 // are those of k_m2l, and so are the results, bit by bit.  USE only names the
-// instance (1: L2L, 2: M2M) so that profiles tell them apart.
+// instance (1: L2L, 2: M2M) so that profiles tell them apart.  level_product says
+// where k_m2l's one wave per 16 rows is the better.
 template <class R, int NT, int USE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 3)))
 k_level(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile_row,
         const int32_t *__restrict__ group_off, const int32_t *__restrict__ group_end, const int32_t *__restrict__ src,
         const int32_t *__restrict__ dest, const R *__restrict__ Tsw, const R *__restrict__ M, R *__restrict__ out) {
+  static_assert(NT >= 4, "every wave has a column tile");
   constexpr bool F64 = sizeof(R) == 8;
   constexpr int W = 16 / sizeof(R);
   constexpr int PS = NT * 16;
@@ -512,7 +516,7 @@ k_level(const int32_t *__restrict__ tile_group, const int32_t *__restrict__ tile
   const int g = tile_group[tile];
   const int end = group_end[g];
   const int row0 = tile_row[tile] + (blockIdx.x & 3) * 16;
-  if (row0 >= end || wave >= NT) return;
+  if (row0 >= end) return;
   const int i = lane & 15, kq = lane >> 4;
   const R *B = Tsw + (size_t)group_off[g] * TB + lane;
   const int sr = src[min(row0 + i, end - 1)];
@@ -1022,7 +1026,7 @@ static_assert(M2LBf<NT_FIXED, RB_FIXED>::CS == P_FIXED * P_FIXED, "compact rows 
 // each with RT = 2 row tiles: 256 rows per tile, the FP32 tile lists) and
 // walks a contiguous, XCD-aware range of tiles, reloading the operator only
 // when the offset group changes.  Per tile the arithmetic is that of
-// k_m2l<double, NT, 2, false> (same operands, same K order), so results
+// k_m2l<double, NT, 2, false, 0> (same operands, same K order), so results
 // are identical; the operator is read from LDS instead of from L2 at every
 // k-step.
 template <int NT>
@@ -2252,24 +2256,43 @@ static void launch_p2m(Tree &T, PrecBufs &B, int src, hipStream_t s) {
   LAUNCH_OK();
 }
 
-// Batched per-level product on the MFMA kernel: for every cell c of level
+// Batched per-level product on the MFMA kernels: for every cell c of level
 // l (l >= 3), out[c - coff[l]] = S_oct(c) in[src[c]], with the per-octant
-// operator table S (M2M: src = the cell, L2L: src = its parent).
+// operator table S (M2M: src = the cell, L2L: src = its parent).  k_level splits
+// the column tiles over waves where that shortens a chain worth it, and takes
+// four times the waves, which have to find room among the near field's.  It stays
+// with levels of up to 100 tiles of 64 rows from order 9 on, 40 at orders 7 and 8
+// (4 column tiles, chains of 64 products), and none below, and with products whose
+// near field leaves room (`crowded` false).  Measured with one wave per 16 rows at
+// every level -> k_level at every level -> this rule, us: FP64 C^T 323 -> 274 -> 274 at
+// 81,920 panels, 684 -> 632 -> 632 at 1.3 million, there FP64 B at order 8 465 -> 493
+// -> 474, at order 4 192 -> 227 -> 192; FP32 A at 655,220 panels and order 8 1231 -> 1274
+// -> 1223.
 template <class R, int USE>
 static void level_product(Tree &T, int l, const int32_t *src, const void *table, const R *in, R *out,
-                          hipStream_t s) {
-  const bool f64 = std::is_same<R, double>::value;
+                          bool crowded, hipStream_t s) {
+  constexpr bool F64 = std::is_same<R, double>::value;
   const Tree::L2LList &LW = T.l2lw;
   const int64_t t0 = LW.t0[l], t1 = LW.t1[l];
   if (t1 <= t0) return;
-  const dim3 grid((unsigned)(4 * (t1 - t0)));  // 16 rows each
-#define LEVEL_CASE(nt)                                                                                          \
-  case nt:                                                                                                      \
-    k_level<R, nt, USE><<<grid, 256, 0, s>>>(LW.tile_group.p + t0, LW.tile_row.p + t0, LW.group_off.p,           \
-                                             LW.group_end.p, src, LW.dest.p, reinterpret_cast<const R *>(table), \
-                                             in, out);                                                          \
+  const int NT = T.ps / 16;
+  const bool split = !crowded && t1 - t0 <= (NT >= 6 ? 100 : NT >= 4 ? 40 : 0);
+  const dim3 grid((unsigned)((split ? 4 : 1) * (t1 - t0)));  // 16 or 64 rows each
+  const auto launch = [&](auto kernel) {
+    kernel<<<grid, 256, 0, s>>>(LW.tile_group.p + t0, LW.tile_row.p + t0, LW.group_off.p, LW.group_end.p, src,
+                                LW.dest.p, reinterpret_cast<const R *>(table), in, out);
+  };
+#define LEVEL_CASE(nt)                                            \
+  case nt:                                                        \
+    if constexpr (nt >= 4) {                                      \
+      if (split) {                                                \
+        launch(k_level<R, nt, USE>);                              \
+        break;                                                    \
+      }                                                           \
+    }                                                             \
+    launch(k_m2l<R, nt, 1, !F64, USE>);                           \
     break;
-  switch (T.ps / 16) {
+  switch (NT) {
     LEVEL_CASE(1)
     LEVEL_CASE(2)
     LEVEL_CASE(3)
@@ -2396,6 +2419,9 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   const bool compact_rows =
       split_m2l || (!f64 && T.m2l_persistent && T.p == P_FIXED && ML.ntiles >= 8 * (int64_t)T.n_cu);
   const int fork_at = !far ? FORK_START : T.fork_at >= 0 ? T.fork_at : (m2l_first ? FORK_AFTER_M2M : FORK_AFTER_P2M);
+  // a near field over panels of more whole chunks than the chip holds waves keeps
+  // every wave slot taken until its last round
+  const bool crowd = combo == 0 && a.nseg == 1 && nchunks > 8 * 4 * (int64_t)T.n_cu;
   auto fork_point = [&]() {
     if (!rq.far_only && ss != s) HIP_OK(hipEventRecord(T.ev_fork, s));
   };
@@ -2461,7 +2487,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
     const void *Sm = f64 ? (const void *)T.t_m2m64 : (const void *)T.t_m2m32;
     R *rows = reinterpret_cast<R *>(B.l2l_out.p);
     for (int l = L; l >= 3; --l) {
-      level_product<R, 2>(T, l, T.l2lw.self.p, Sm, M, rows, s);
+      level_product<R, 2>(T, l, T.l2lw.self.p, Sm, M, rows, crowd && fork_at < FORK_AFTER_M2M, s);
       const int64_t CP = T.ncell[l - 1];
       k_m2m_sum<R><<<cdiv(CP * ps, TB), TB, 0, s>>>(ps, T.coff[l - 1], CP, T.coff[l], T.cchild.p, rows, M);
       LAUNCH_OK();
@@ -2481,7 +2507,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l64,      \
           reinterpret_cast<const double *>(M), reinterpret_cast<double *>(m2l), (int)ML.ntiles);               \
     else if (f64)                                                                                              \
-      k_m2l<double, nt, M2L_RT64, false><<<dim3((unsigned)ML.ntiles64), 256, 0, s>>>(                         \
+      k_m2l<double, nt, M2L_RT64, false, 0><<<dim3((unsigned)ML.ntiles64), 256, 0, s>>>(                         \
           ML.tile_group64.p, ML.tile_row64.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l64,             \
           reinterpret_cast<const double *>(M), reinterpret_cast<double *>(m2l));                               \
     else if (T.m2l_persistent)                                                                                  \
@@ -2490,7 +2516,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l32,      \
           reinterpret_cast<const float *>(M), reinterpret_cast<float *>(m2l), (int)ML.ntiles);                 \
     else                                                                                                       \
-      k_m2l<float, nt, M2L_RT32, true><<<dim3((unsigned)ML.ntiles), 256, 0, s>>>(                              \
+      k_m2l<float, nt, M2L_RT32, true, 0><<<dim3((unsigned)ML.ntiles), 256, 0, s>>>(                              \
           ML.tile_group.p, ML.tile_row.p, ML.group_off.p, ML.group_end.p, ML.src.p, ML.dest.p, T.t_m2l32,                 \
           reinterpret_cast<const float *>(M), reinterpret_cast<float *>(m2l));                                 \
     break;
@@ -2531,7 +2557,8 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
       const bool leaf = (l == L);
       if (l > 2) {
         // L2L of every cell of level l from its parent's final expansion
-        level_product<R, 1>(T, l, LW.src.p, f64 ? (const void *)T.t_l2l64 : (const void *)T.t_l2l32, Lx, l2l, s);
+        level_product<R, 1>(T, l, LW.src.p, f64 ? (const void *)T.t_l2l64 : (const void *)T.t_l2l32, Lx, l2l,
+                            crowd, s);
       }
       // levels with few cells (long interaction lists, too few waves to hide
       // the load latency) take four waves per cell
@@ -2612,9 +2639,9 @@ void fmm_apply(Tree &T, int precision, const FmmRequest &rq, hipStream_t s) {
 void level_product64(Tree &T, int l, const int32_t *src, const double *table, const double *in, double *out,
                      bool m2m, hipStream_t s) {
   if (m2m)
-    level_product<double, 2>(T, l, src, table, in, out, s);
+    level_product<double, 2>(T, l, src, table, in, out, false, s);
   else
-    level_product<double, 1>(T, l, src, table, in, out, s);
+    level_product<double, 1>(T, l, src, table, in, out, false, s);
 }
 
 void m2m_sum64(Tree &T, int l, const double *rows, double *M, hipStream_t s) {
@@ -2628,7 +2655,7 @@ void m2l_tiles64(const Tree::M2LList &ML, int ps, const double *table, const dou
   const dim3 grid((unsigned)ML.ntiles64);
 #define M2L64_CASE(nt)                                                                                      \
   case nt:                                                                                                  \
-    k_m2l<double, nt, M2L_RT64, false><<<grid, 256, 0, s>>>(ML.tile_group64.p, ML.tile_row64.p,         \
+    k_m2l<double, nt, M2L_RT64, false, 0><<<grid, 256, 0, s>>>(ML.tile_group64.p, ML.tile_row64.p,         \
                                                                 ML.group_off.p, ML.group_end.p, ML.src.p,  \
                                                                 ML.dest.p, table, M, out);                 \
     break;
