@@ -54,9 +54,9 @@
  *   products instead of bf16 ones on operands split into three bf16 parts
  *   (products from or to charges always use the FP32 ones);
  *   BEMFMM_FORK_AT=0, 1, 2 or 3 starts the near field at the start of the
- *   product, after P2M, after M2M or after M2L (default: after M2M when the
- *   M2L has at least 32 tiles of 256 pairs per compute unit, or 8 for the
- *   split-bf16 FP32 M2L, else after P2M);
+ *   product, after P2M, after M2M or after M2L (default: after M2M where the
+ *   M2L is the longer part or the near field runs in short parts, else after
+ *   P2M);
  *   BEMFMM_NEAR_PARTS=1..32 splits the sources of every near field into so
  *   many parts (1: none; default: by the number of targets and the length of
  *   the near lists);

@@ -2386,16 +2386,6 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   const bool nq = !rq.far_only && nchunks > 0 && T.n_nq > 0 && (rq.op == BEMFMM_OP_A || rq.op == BEMFMM_OP_AT);
   a.nq_out = nq ? B.nq_out.p : nullptr;
   B.last_tgt = rq.tgt;
-  // The near field runs on the second stream, forked from the caller's
-  // stream at a point of the upward pass and joined before L2P.  In FP32 and
-  // with a persistent M2L (FP64: at least 32 tiles of 256 pairs per CU) it
-  // forks after M2M: the few small kernels of the M2M would wait for near-field
-  // waves to retire, and the M2L's workgroups are resident first.  Forked after
-  // P2M instead, the FP32 A product takes 339 instead of 303 us at 81,920
-  // panels and 1032 instead of 941 us at 327,680, and A^T 217 instead of 184 us at
-  // 46,080.  The smaller FP64 M2L runs one tile per workgroup, which near-field
-  // waves hold up wherever they start; after P2M is the better there (327,680
-  // panels 1.83 against 1.85 ms).
   const int combo = src_charges ? 1 : (rq.tgt == TGT_CHARGE ? 2 : 0);
   const Tree::M2LList &ML = T.m2l[combo];
   const bool far = (L >= 2) && T.nfar > 0;
@@ -2409,7 +2399,32 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   // solve.
   const bool split_m2l =
       !f64 && combo == 0 && T.m2l_persistent && T.m2l_split && T.p == P_FIXED && T.t_m2lbf;
-  const bool m2l_first = !f64 || big_m2l;
+  // The near field runs on the second stream, forked from the caller's stream at
+  // a point of the upward pass and joined before L2P.  After P2M it starts
+  // soonest; after M2M the few small kernels of the M2M do not wait for its waves
+  // to retire, and the M2L, enqueued first, has its workgroups resident.  The
+  // second is the better where the M2L is the longer part or the near field's waves
+  // are short (parts); a near field of long whole chunks that comes late has waves
+  // left over when the M2L ends.  FP32, after P2M : after M2M, us (tiles: of 256
+  // M2L pairs, per CU):
+  //   products with charges, whose near fields are short, from order 9 on, and below
+  //     over more than 4 chunks per SIMD: B at 81,920 panels 245 : 198; at order 4 there
+  //     82 : 88, at 327,680 panels 121 : 109
+  //   A and A^T in parts, from order 9 on: A at 81,920 panels 329 : 295; below, from 8
+  //     tiles on: A^T of order 8 at 162,000 panels (14) 462 : 434, but A at 81,920 (3)
+  //     264 : 281
+  //   in whole chunks, at orders 10 and 11, from 8 tiles on: A at 327,680 panels (14)
+  //     1002 : 930, but at ncrit 256 (3) 2147 : 2714; below, from 32 on: order 6 at 655,220
+  //     panels (57) 1212 : 1060, but at 327,680 (14) 769 : 802
+  // FP64: with a persistent M2L, and gradients in parts from order 9 and 2 tiles on (A
+  // at 81,920 panels, 3 tiles, 532 : 509, at 20,480, 0.7, 182 : 186); otherwise the near
+  // field's waves hold up the M2L of one tile per workgroup wherever they start (A^T
+  // at 81,920 panels 505 : 512).
+  const int64_t simds = 4 * (int64_t)T.n_cu;
+  const int fork_tiles = a.nseg > 1 ? (ps >= 96 ? 0 : 8) : (ps >= 112 ? 8 : 32);
+  const bool m2l_first =
+      f64 ? big_m2l || (a.nseg > 1 && rq.out == OUT_NGRAD && ps >= 96 && ML.ntiles >= 2 * (int64_t)T.n_cu)
+          : (combo != 0 ? ps >= 96 || nchunks > 4 * simds : ML.ntiles >= fork_tiles * (int64_t)T.n_cu);
   // M2L result rows without the padding places (read so by the downward pass).
   // The FP32 MFMA kernel scatters them into its staging area at four times the
   // lane stride, which costs it more LDS time than the bytes give on short
