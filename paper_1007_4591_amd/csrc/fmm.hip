@@ -2434,9 +2434,12 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   const bool compact_rows =
       split_m2l || (!f64 && T.m2l_persistent && T.p == P_FIXED && ML.ntiles >= 8 * (int64_t)T.n_cu);
   const int fork_at = !far ? FORK_START : T.fork_at >= 0 ? T.fork_at : (m2l_first ? FORK_AFTER_M2M : FORK_AFTER_P2M);
-  // a near field over panels of more whole chunks than the chip holds waves keeps
-  // every wave slot taken until its last round
-  const bool crowd = combo == 0 && a.nseg == 1 && nchunks > 8 * 4 * (int64_t)T.n_cu;
+  // Whole chunks of a near field over panels keep the wave slots taken: an M2M behind
+  // their start from 4 per SIMD on, an L2L from 8 on, where they outlast the M2L
+  // (level_product; FP32 A of order 9 at 233,280 panels 742 -> 716 us, FP64 A of order
+  // 10 there 1375 -> 1352)
+  const int64_t near_waves = combo == 0 && a.nseg == 1 ? nchunks : 0;
+  const bool crowd_m2m = near_waves > 4 * simds && fork_at < FORK_AFTER_M2M, crowd_l2l = near_waves > 8 * simds;
   auto fork_point = [&]() {
     if (!rq.far_only && ss != s) HIP_OK(hipEventRecord(T.ev_fork, s));
   };
@@ -2502,7 +2505,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
     const void *Sm = f64 ? (const void *)T.t_m2m64 : (const void *)T.t_m2m32;
     R *rows = reinterpret_cast<R *>(B.l2l_out.p);
     for (int l = L; l >= 3; --l) {
-      level_product<R, 2>(T, l, T.l2lw.self.p, Sm, M, rows, crowd && fork_at < FORK_AFTER_M2M, s);
+      level_product<R, 2>(T, l, T.l2lw.self.p, Sm, M, rows, crowd_m2m, s);
       const int64_t CP = T.ncell[l - 1];
       k_m2m_sum<R><<<cdiv(CP * ps, TB), TB, 0, s>>>(ps, T.coff[l - 1], CP, T.coff[l], T.cchild.p, rows, M);
       LAUNCH_OK();
@@ -2573,7 +2576,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
       if (l > 2) {
         // L2L of every cell of level l from its parent's final expansion
         level_product<R, 1>(T, l, LW.src.p, f64 ? (const void *)T.t_l2l64 : (const void *)T.t_l2l32, Lx, l2l,
-                            crowd, s);
+                            crowd_l2l, s);
       }
       // levels with few cells (long interaction lists, too few waves to hide
       // the load latency) take four waves per cell
