@@ -377,7 +377,7 @@ void radix_sort_u32(uint32_t *keys, int32_t *vals, int64_t n, int bits, hipStrea
 // fmm.hip
 // parts the near field of a target chunk is split into, one wave each, for
 // products that keep `sums` near sums per target
-int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, int sums);
+int near_parts(const Tree &T, bool f64, bool src_charges, bool tgt_charges, int64_t nchunks, int sums);
 
 enum SrcKind { SRC_PANEL_MONO = 0, SRC_PANEL_DIP = 1, SRC_PANEL_MONODIP = 2, SRC_CHARGE_MONO = 3 };
 enum TgtKind { TGT_PANEL = 0, TGT_CHARGE = 1 };

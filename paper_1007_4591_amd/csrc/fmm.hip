@@ -2127,15 +2127,24 @@ static void prof_collect(Tree &T) {
 // panels 266 -> 217 and 327 -> 243 us; FP64 A at 81,920 and 128,000 panels 637 ->
 // 571 and 1099 -> 857 us) and lose above, where FP32 writes three totals per
 // target and near leaf, and FP64 holds up the M2L beside it (184,320 panels:
-// FP32 559 -> 604, FP64 1248 -> 1287 us).
-int near_parts(const Tree &T, bool src_charges, bool tgt_charges, int64_t nchunks, int sums) {
-  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32;
+// FP32 559 -> 604, FP64 1248 -> 1287 us).  FP32 writes and reads a total per lane and
+// near leaf, which has to be worth the leaf's sources where the chip is not idle
+// anyway: from 3 chunks per CU on at least 16 of them, and 40 above 4 chunks per
+// SIMD, where a chunk gets two parts.  FP32, parts : whole chunks, us, by sources per
+// near leaf: A over 900 chunks 204 : 172 at 7, over 1,700 210 : 175 at 12, 212 : 205 at 19, 217 : 256
+// at 27, A^T 195 : 172 at 12, 190 : 233 at 19; B over 2,400 chunks 320 : 238 at 4; A^T over
+// 5,100 to 7,500 chunks 483 : 457 at 16, 490 : 461 at 25, 518 : 506 at 31, 790 : 752 at 34, 660 :
+// 737 at 44; but C^T over 130 chunks 70 : 84 at 3, over 700 107 : 117.
+int near_parts(const Tree &T, bool f64, bool src_charges, bool tgt_charges, int64_t nchunks, int sums) {
+  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32, MIN_LEAF = 16, MIN_LEAF_TWO = 40;
   const int64_t simds = 4 * (int64_t)T.n_cu;
   if (nchunks <= 0) return 1;
   if (T.near_parts > 0) return T.near_parts;
   if (sums > 1 && nchunks > 4 * simds) return 1;
   const int64_t npts = std::max<int64_t>(tgt_charges ? T.Q : T.N, 1);
   const int64_t mean = T.near_pairs[src_charges][tgt_charges] / npts;  // sources per target
+  const int64_t leaf = mean * T.ncell[T.L] / std::max<int64_t>(T.n_near_leaf, 1);  // and near leaf
+  if (!f64 && nchunks > 3 * T.n_cu && leaf < (nchunks > 4 * simds ? MIN_LEAF_TWO : MIN_LEAF)) return 1;
   const int64_t want = cdiv(WAVES_PER_SIMD * simds, nchunks);
   return (int)std::max<int64_t>(1, std::min(std::min(want, mean / MIN_SOURCES), MAX_PARTS));
 }
@@ -2153,7 +2162,7 @@ static NearPlan near_plan(const Tree &T, bool f64, bool whole, bool src_charges,
   const int64_t nchunks = tgt_charges ? T.nchunk_q : T.nchunk_p, ntgt = tgt_charges ? T.Q : T.N;
   const int nc = near_ncomp(out);
   NearPlan P;
-  P.nseg = whole ? 1 : near_parts(T, src_charges, tgt_charges, nchunks, nc);
+  P.nseg = whole ? 1 : near_parts(T, f64, src_charges, tgt_charges, nchunks, nc);
   // leaf totals of FP32 parts: 0.1 GB at 81,920 panels; the near lists of a small
   // theta are longer, and beyond 1 GB the chunks stay whole
   P.leaf = (size_t)nchunks * T.near_max * nc * 64;

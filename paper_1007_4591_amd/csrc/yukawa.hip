@@ -743,7 +743,7 @@ void lpb_setup(Tree &T, double kappa, hipStream_t s) {
     S.w.alloc(N);
     S.uvs.alloc(N);
     S.yk.alloc(N);
-    S.nseg = near_parts(T, false, false, T.nchunk_p, 1);
+    S.nseg = near_parts(T, true, false, false, T.nchunk_p, 1);
     S.nr.alloc((size_t)S.nseg * N);
     S.lap4.alloc(4 * N);
     S.wd0.alloc(N);

@@ -73,10 +73,11 @@ def test_product_after_one_that_found_no_memory(prec):
     B.tree_destroy(t)
 
 
-def test_near_field_without_room_for_its_parts():
+def test_near_field_without_room_for_its_parts(monkeypatch):
     """FP32 leaf totals are scratch that only a near field in parts needs: with
     room for half of them the product runs whole chunks, to the same bits."""
     B = lib()
+    monkeypatch.setenv("BEMFMM_NEAR_PARTS", "4")
     p, t = _build(B)
     x = dev(np.random.default_rng(2).normal(size=p.n_panels))
     near = np.diff(B.tree_export(t)["near_ptr"]).max()
