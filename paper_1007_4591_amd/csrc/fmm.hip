@@ -2270,13 +2270,14 @@ static void launch_p2m(Tree &T, PrecBufs &B, int src, hipStream_t s) {
 // operator table S (M2M: src = the cell, L2L: src = its parent).  k_level splits
 // the column tiles over waves where that shortens a chain worth it, and takes
 // four times the waves, which have to find room among the near field's.  It stays
-// with levels of up to 100 tiles of 64 rows from order 9 on, 40 at orders 7 and 8
+// with levels of up to 200 tiles of 64 rows from order 9 on, 40 at orders 7 and 8
 // (4 column tiles, chains of 64 products), and none below, and with products whose
 // near field leaves room (`crowded` false).  Measured with one wave per 16 rows at
-// every level -> k_level at every level -> this rule, us: FP64 C^T 323 -> 274 -> 274 at
-// 81,920 panels, 684 -> 632 -> 632 at 1.3 million, there FP64 B at order 8 465 -> 493
-// -> 474, at order 4 192 -> 227 -> 192; FP32 A at 655,220 panels and order 8 1231 -> 1274
-// -> 1223.
+// every level -> k_level at every level -> this rule, us: FP64 C^T at 81,920 panels 323
+// -> 274 -> 274, at 1.3 million 684 -> 632 -> 632; FP64 B there at order 8 465 -> 493 -> 474, at
+// order 4 192 -> 227 -> 192; FP32 A at 655,220 panels and order 8 1231 -> 1274 -> 1223.
+// Leaf levels at order 10, whole : split: C^T of 117 tiles 494 : 484 us, B of 285 tiles
+// 656 : 667 us (FP64).
 template <class R, int USE>
 static void level_product(Tree &T, int l, const int32_t *src, const void *table, const R *in, R *out,
                           bool crowded, hipStream_t s) {
@@ -2285,7 +2286,7 @@ static void level_product(Tree &T, int l, const int32_t *src, const void *table,
   const int64_t t0 = LW.t0[l], t1 = LW.t1[l];
   if (t1 <= t0) return;
   const int NT = T.ps / 16;
-  const bool split = !crowded && t1 - t0 <= (NT >= 6 ? 100 : NT >= 4 ? 40 : 0);
+  const bool split = !crowded && t1 - t0 <= (NT >= 6 ? 200 : NT >= 4 ? 40 : 0);
   const dim3 grid((unsigned)((split ? 4 : 1) * (t1 - t0)));  // 16 or 64 rows each
   const auto launch = [&](auto kernel) {
     kernel<<<grid, 256, 0, s>>>(LW.tile_group.p + t0, LW.tile_row.p + t0, LW.group_off.p, LW.group_end.p, src,
