@@ -348,9 +348,9 @@ struct Tree {
   // stage times per [product kind: the six operators, then any other][FP64, FP32][stage]
   double prof_ms[7][2][7] = {};
   int64_t prof_cnt[7][2][7] = {};
-  bool prof_pending[7] = {false, false, false, false, false, false, false};
+  bool prof_pending[8] = {};
   int prof_kind = 6, prof_prec = 0;  // product being timed
-  hipEvent_t ev[14] = {};
+  hipEvent_t ev[16] = {};
   bool ev_init = false;
 
   int last_op32 = -1, last_op64 = -1;
@@ -442,7 +442,7 @@ void lpb_solve(Tree &T, const double *q, double kappa, double *uv, double tol, i
 double lpb_energy(Tree &T, const double *q, const double *uv, hipStream_t s);
 
 // profiling helpers (fmm.hip)
-enum Stage { ST_P2M = 0, ST_M2M = 1, ST_M2L = 2, ST_L2L = 3, ST_P2P = 4, ST_OTHER = 5, ST_L2P = 6 };
+enum Stage { ST_P2M = 0, ST_M2M = 1, ST_M2L = 2, ST_L2L = 3, ST_P2P = 4, ST_OTHER = 5, ST_L2P = 6, ST_NEARQUAD = 7 };
 void prof_begin(Tree &T, int stage, hipStream_t s);
 void prof_end(Tree &T, int stage, hipStream_t s);
 

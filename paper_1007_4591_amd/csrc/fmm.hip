@@ -2100,13 +2100,14 @@ void prof_end(Tree &T, int stage, hipStream_t s) {
 
 static void prof_collect(Tree &T) {
   if (!T.prof_now) return;
-  for (int st = 0; st < 7; ++st) {
+  for (int st = 0; st <= ST_NEARQUAD; ++st) {
     if (!T.prof_pending[st]) continue;
     HIP_OK(hipEventSynchronize(T.ev[2 * st + 1]));
     float ms = 0.f;
     HIP_OK(hipEventElapsedTime(&ms, T.ev[2 * st], T.ev[2 * st + 1]));
-    T.prof_ms[T.prof_kind][T.prof_prec][st] += ms;
-    T.prof_cnt[T.prof_kind][T.prof_prec][st] += 1;
+    // (near quadrature is reported with the near field it belongs to)
+    T.prof_ms[T.prof_kind][T.prof_prec][st == ST_NEARQUAD ? (int)ST_P2P : st] += ms;
+    if (st != ST_NEARQUAD) T.prof_cnt[T.prof_kind][T.prof_prec][st] += 1;
     T.prof_pending[st] = false;
   }
 }
@@ -2497,10 +2498,12 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
     const bool tr = rq.op == BEMFMM_OP_AT;
     fork_point();
     if (ss != s) HIP_OK(hipStreamWaitEvent(ss, T.ev_fork, 0));
+    prof_begin(T, ST_NEARQUAD, ss);
     k_nq_apply<R><<<cdiv(T.N, 256), 256, 0, ss>>>(
         T.N, tr ? T.nqT_ptr.p : T.nq_ptr.p, tr ? T.nqT_idx.p : T.nq_idx.p, tr ? T.nqT_coef.p : T.nq_coef.p,
         tr ? rq.wdip : rq.wmono, tr ? reinterpret_cast<const R4 *>(a.tgt_pos) : nullptr, B.nq_out.p);
     LAUNCH_OK();
+    prof_end(T, ST_NEARQUAD, ss);
   }
   if (fork_at == FORK_START) fork_near();
 
