@@ -1369,31 +1369,49 @@ __device__ __forceinline__ void pair_accumulate(const typename V4<R>::T &s4, con
 // K' or of K'^T, see the tree's nq lists), which the combine adds to the near
 // field.  For A^T the sum is divided by the target's area as the product
 // stores it (the combine multiplies the near field by that same area).
-// Bound by memory: 12 bytes per pair, in runs, and x at about 11 places per
-// row.  A workgroup takes 256 rows, one run of the list: its coefficients and
-// values are loaded 2048 at a time in runs and go through LDS, where each thread
-// adds its own row in order.  With a thread reading its own row the kernel took 170
-// us at 655,220 panels (7.5 million pairs), and ran after the near field; now 91
-// us, beside the upward pass.
+// Bound by memory: 12 bytes per pair and x at as many places as a row has pairs
+// (11 at nu = 2, 680 at 16).  A wave takes 64 rows, NQ_SEG pairs of each at a time:
+// NQ_SEG lanes load those of one row, which stand side by side in the list, and
+// through LDS every lane adds its own row in order, so all lanes have work whatever
+// the length of the rows.  FP32 A, a thread reading its own row -> 256 rows' pairs in
+// list order, 2048 at a time, added by the few threads whose rows are at hand ->
+// this, us: 655,220 panels at nu = 2 1694 -> 1572 -> 1562, 20,480 at nu = 6 370 -> 193 -> 125,
+// at nu = 16 1083 -> 2797 -> 241.  NQ_SEG 8 took 1605 at nu = 3 on 655,220 panels (1580), 4
+// 1663.
+constexpr int NQ_SEG = 16;
+
 template <class R>
-__global__ void __launch_bounds__(256) k_nq_apply(int64_t n, const int32_t *__restrict__ ptr,
-                                                  const int32_t *__restrict__ idx, const double *__restrict__ coef,
-                                                  const double *__restrict__ x,
-                                                  const typename V4<R>::T *__restrict__ tgt_pos,
-                                                  double *__restrict__ out) {
-  constexpr int TILE = 2048;
-  __shared__ double2 pair[TILE];
-  const int64_t t0 = (int64_t)blockIdx.x * 256, t = t0 + threadIdx.x;
-  const int b = ptr[t0], e = ptr[min(t0 + 256, n)];
-  int k = t < n ? ptr[t] : 0;
-  const int ke = t < n ? ptr[t + 1] : 0;
+__global__ void __launch_bounds__(64) k_nq_apply(int64_t n, const int32_t *__restrict__ ptr,
+                                                 const int32_t *__restrict__ idx, const double *__restrict__ coef,
+                                                 const double *__restrict__ x,
+                                                 const typename V4<R>::T *__restrict__ tgt_pos,
+                                                 double *__restrict__ out) {
+  constexpr int PER = 64 / NQ_SEG, NROW = 64 / PER;  // rows loaded at a time, and times
+  __shared__ double2 seg[64][NQ_SEG + 1];
+  const int lane = threadIdx.x, sub = lane % NQ_SEG, grp = lane / NQ_SEG;
+  const int64_t t = (int64_t)blockIdx.x * 64 + lane;
+  const int k = t < n ? ptr[t] : 0, len = t < n ? ptr[t + 1] - k : 0;
+  int longest = len;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
   double acc = 0.0;
-  for (int base = b; base < e; base += TILE) {
-    const int end = min(base + TILE, e);
+  for (int o = 0; o < longest; o += NQ_SEG) {
+    double c[NROW], v[NROW];
+    int at[NROW];
+#pragma unroll
+    for (int r = 0; r < NROW; ++r) {
+      const int row = r * PER + grp, i = __shfl(k, row) + o + sub;
+      const bool in = o + sub < __shfl(len, row);
+      c[r] = in ? coef[i] : 0.0;
+      at[r] = in ? idx[i] : -1;
+    }
+#pragma unroll
+    for (int r = 0; r < NROW; ++r) v[r] = at[r] >= 0 ? x[at[r]] : 0.0;
     __syncthreads();  // the previous pairs are no longer read
-    for (int i = base + threadIdx.x; i < end; i += 256) pair[i - base] = make_double2(coef[i], x[idx[i]]);
+#pragma unroll
+    for (int r = 0; r < NROW; ++r) seg[r * PER + grp][sub] = make_double2(c[r], v[r]);
     __syncthreads();
-    for (; k < min(ke, end); ++k) acc = fma_(pair[k - base].x, pair[k - base].y, acc);
+    for (int j = 0; j < min(NQ_SEG, len - o); ++j) acc = fma_(seg[lane][j].x, seg[lane][j].y, acc);
   }
   if (t >= n) return;
   if (tgt_pos) acc /= (double)tgt_pos[t].w;
@@ -2499,7 +2517,7 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
     fork_point();
     if (ss != s) HIP_OK(hipStreamWaitEvent(ss, T.ev_fork, 0));
     prof_begin(T, ST_NEARQUAD, ss);
-    k_nq_apply<R><<<cdiv(T.N, 256), 256, 0, ss>>>(
+    k_nq_apply<R><<<cdiv(T.N, 64), 64, 0, ss>>>(
         T.N, tr ? T.nqT_ptr.p : T.nq_ptr.p, tr ? T.nqT_idx.p : T.nq_idx.p, tr ? T.nqT_coef.p : T.nq_coef.p,
         tr ? rq.wdip : rq.wmono, tr ? reinterpret_cast<const R4 *>(a.tgt_pos) : nullptr, B.nq_out.p);
     LAUNCH_OK();
