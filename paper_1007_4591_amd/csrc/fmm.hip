@@ -2434,8 +2434,8 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   // to retire, and the M2L, enqueued first, has its workgroups resident.  The
   // second is the better where the M2L is the longer part or the near field's waves
   // are short (parts); a near field of long whole chunks that comes late has waves
-  // left over when the M2L ends.  FP32, after P2M : after M2M, us (tiles: of 256
-  // M2L pairs, per CU):
+  // left over when the M2L ends.  FP32, after P2M : after M2M, us (tiles: 256
+  // M2L pairs, per CU, were every tile full):
   //   products with charges, whose near fields are short, from order 9 on, and below
   //     over more than 4 chunks per SIMD: B at 81,920 panels 245 : 198; at order 4 there
   //     82 : 88, at 327,680 panels 121 : 109
@@ -2449,11 +2449,11 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   // at 81,920 panels, 3 tiles, 532 : 509, at 20,480, 0.7, 182 : 186); otherwise the near
   // field's waves hold up the M2L of one tile per workgroup wherever they start (A^T
   // at 81,920 panels 505 : 512).
-  const int64_t simds = 4 * (int64_t)T.n_cu;
+  const int64_t simds = 4 * (int64_t)T.n_cu, per_cu = M2L_ROWS32 * (int64_t)T.n_cu;
   const int fork_tiles = a.nseg > 1 ? (ps >= 96 ? 0 : 8) : (ps >= 112 ? 8 : 32);
   const bool m2l_first =
-      f64 ? big_m2l || (a.nseg > 1 && rq.out == OUT_NGRAD && ps >= 96 && ML.ntiles >= 2 * (int64_t)T.n_cu)
-          : (combo != 0 ? ps >= 96 || nchunks > 4 * simds : ML.ntiles >= fork_tiles * (int64_t)T.n_cu);
+      f64 ? big_m2l || (a.nseg > 1 && rq.out == OUT_NGRAD && ps >= 96 && ML.n >= 2 * per_cu)
+          : (combo != 0 ? ps >= 96 || nchunks > 4 * simds : ML.n >= fork_tiles * per_cu);
   // M2L result rows without the padding places (read so by the downward pass).
   // The FP32 MFMA kernel scatters them into its staging area at four times the
   // lane stride, which costs it more LDS time than the bytes give on short
