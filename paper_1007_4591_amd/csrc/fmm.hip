@@ -1275,9 +1275,10 @@ __global__ void __launch_bounds__(256) k_downward(int p, int ps, int rs, int com
 // One source-target pair.  Monopole: lp += w/r, (lx,ly,lz) += w d/r^3 (=
 // -grad).  Dipole m: lp += m.d/r^3, (lx,ly,lz) += 3 (m.d) d/r^5 - m/r^3 (=
 // -grad).  d = target - source, ri = 1/r (0 for the excluded self pair).
-// Every fused multiply-add is written out, so that the rounding of a pair does
-// not depend on how the compiler contracts the loop around it: the near field
-// gives the same bits from every path it takes.
+// Every fused multiply-add is written out, so that a pair rounds the same way on
+// every path, however the compiler contracts the loop around it.  The FP32 near
+// field then gives the same bits from every path; FP64 parts cut leaves and sum
+// each piece, so there a split changes the last bits.
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -2139,9 +2140,10 @@ static void prof_collect(Tree &T) {
 // Measured on an MI355X, whole chunks -> this rule: FP64 solve, 1,280 panels
 // (24 chunks) 1319 -> 862 us; FP64 A^T, 327,680 panels (7,415 chunks) 2.10 ->
 // 1.82 ms; FP32 A, 5,120 panels 203 -> 72 us, 20,480 panels (452 chunks) 254 ->
-// 153 us.
+// 127 us.
 // One sum per target (the potential) gains throughout: FP32 A^T at 128,000
-// panels 603 -> 533 us, at 327,680 981 -> 917 us.  With the three of a
+// panels 603 -> 533 us, at 327,680 981 -> 917 us, C and B^T of 64 molecules (7,635
+// chunks of charges) 1.58 -> 1.54 and 1.74 -> 1.68 ms.  With the three of a
 // gradient, parts gain up to 4 chunks per SIMD (FP32 A at 46,080 and 62,720
 // panels 266 -> 217 and 327 -> 243 us; FP64 A at 81,920 and 128,000 panels 637 ->
 // 571 and 1099 -> 857 us) and lose above, where FP32 writes three totals per

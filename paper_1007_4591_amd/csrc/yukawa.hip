@@ -743,6 +743,10 @@ void lpb_setup(Tree &T, double kappa, hipStream_t s) {
     S.w.alloc(N);
     S.uvs.alloc(N);
     S.yk.alloc(N);
+    // (two sums per target, but FP64 ones, added plainly, with no M2L beside the
+    // start of them: parts gain up to 8 chunks per SIMD, like one sum; whole chunks
+    // against parts per product: 184,320 panels 3.59 -> 2.98 ms, 242,000 4.53 -> 3.90, 327,680
+    // 6.21 -> 5.45)
     S.nseg = near_parts(T, true, false, false, T.nchunk_p, 1);
     S.nr.alloc((size_t)S.nseg * N);
     S.lap4.alloc(4 * N);
@@ -857,7 +861,11 @@ void lpb_matvec(Tree &T, double kappa, const double *uv, double *y, hipStream_t 
   // the screened far field, whose kernels are MFMA-bound (M2L) or too small to
   // fill the chip (the per-level ones).  Started before the Laplace far field
   // its waves hold up both chains (46,080 panels, solve: 17.3 against 16.8 ms),
-  // after both it has nothing beside it (19.1 ms).
+  // after both it has nothing beside it (19.1 ms).  Where it fills the chip by
+  // itself little of that remains: at 1.3 million panels k_yk_p2m, 51 KB of LDS per
+  // wave, waits for its waves to retire (12 ms inside its launch, 1.0 in line), and
+  // the product takes 19.1 ms against 21.6 in line.  Started after the screened M2M
+  // is not measured.
   const hipStream_t ss = T.concurrent ? T.side_stream : s;
   if (T.nchunk_p > 0) {
     HIP_OK(hipEventRecord(T.ev_fork, s));

@@ -51,3 +51,24 @@ def test_capture_after_a_product_of_another_kind(prec, near_quad, no_collection)
             got = host(out)
             assert np.array_equal(got, host(B.fmm_matvec(t, op, prec, inp))), (op, rep)
     B.tree_destroy(t)
+
+
+def test_capture_of_the_screened_product(no_collection):
+    import torch
+    B = lib()
+    p = synth.blobby(4, n_charges=20)
+    t = B.build_tree(p.verts, p.tris, p.charge_pos, B.Params(ncrit=32))
+    rng = np.random.default_rng(4)
+    z = dev(rng.normal(size=2 * p.n_panels))
+    out = torch.empty_like(z)
+    B.lpb_matvec(t, 0.2, z)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.lpb_matvec(t, 0.2, z, y=out)
+    for rep in range(3):
+        z.copy_(dev(rng.normal(size=z.numel())))
+        g.replay()
+        got = host(out)
+        assert np.array_equal(got, host(B.lpb_matvec(t, 0.2, z))), rep
+    B.tree_destroy(t)
