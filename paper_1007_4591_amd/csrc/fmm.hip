@@ -2150,14 +2150,14 @@ static void prof_collect(Tree &T) {
 // target and near leaf, and FP64 holds up the M2L beside it (184,320 panels:
 // FP32 559 -> 604, FP64 1248 -> 1287 us).  FP32 writes and reads a total per lane and
 // near leaf, which has to be worth the leaf's sources where the chip is not idle
-// anyway: from 3 chunks per CU on at least 16 of them, and 40 above 4 chunks per
+// anyway: from 3 chunks per CU on at least 16 of them, and 48 above 4 chunks per
 // SIMD, where a chunk gets two parts.  FP32, parts : whole chunks, us, by sources per
 // near leaf: A over 900 chunks 204 : 172 at 7, over 1,700 210 : 175 at 12, 212 : 205 at 19, 217 : 256
 // at 27, A^T 195 : 172 at 12, 190 : 233 at 19; B over 2,400 chunks 320 : 238 at 4; A^T over
-// 5,100 to 7,500 chunks 483 : 457 at 16, 490 : 461 at 25, 518 : 506 at 31, 790 : 752 at 34, 660 :
-// 737 at 44; but C^T over 130 chunks 70 : 84 at 3, over 700 107 : 117.
+// 5,100 to 7,500 chunks 461 : 435 at 12, 483 : 457 at 22, 490 : 461 at 34, 790 : 752 at 36, 518 :
+// 506 at 43, 660 : 737 at 61; but C^T over 130 chunks 70 : 84 at 3, over 700 107 : 117.
 int near_parts(const Tree &T, bool f64, bool src_charges, bool tgt_charges, int64_t nchunks, int sums) {
-  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32, MIN_LEAF = 16, MIN_LEAF_TWO = 40;
+  constexpr int64_t WAVES_PER_SIMD = 8, MIN_SOURCES = 64, MAX_PARTS = 32, MIN_LEAF = 16, MIN_LEAF_TWO = 48;
   const int64_t simds = 4 * (int64_t)T.n_cu;
   if (nchunks <= 0) return 1;
   if (T.near_parts > 0) return T.near_parts;
@@ -2445,14 +2445,17 @@ static void run_fmm(Tree &T, PrecBufs &B, const FmmRequest &rq, hipStream_t s) {
   //     tiles on: A^T of order 8 at 162,000 panels (14) 462 : 434, but A at 81,920 (3)
   //     264 : 281
   //   in whole chunks, at orders 10 and 11, from 8 tiles on: A at 327,680 panels (14)
-  //     1002 : 930, but at ncrit 256 (3) 2147 : 2714; below, from 32 on: order 6 at 655,220
-  //     panels (57) 1212 : 1060, but at 327,680 (14) 769 : 802
+  //     1002 : 930, but at ncrit 256 (3) 2147 : 2714, and from any with less than 700
+  //     sources per target: at theta 0.9 and 162,000 panels (569 sources) 245 : 209, at
+  //     233,280 (820) 270 : 280; below order 10 from 32 on: order 6 at 655,220 panels (57)
+  //     1212 : 1060, but at 327,680 (14) 769 : 802
   // FP64: with a persistent M2L, and gradients in parts from order 9 and 2 tiles on (A
   // at 81,920 panels, 3 tiles, 532 : 509, at 20,480, 0.7, 182 : 186); otherwise the near
   // field's waves hold up the M2L of one tile per workgroup wherever they start (A^T
   // at 81,920 panels 505 : 512).
   const int64_t simds = 4 * (int64_t)T.n_cu, per_cu = M2L_ROWS32 * (int64_t)T.n_cu;
-  const int fork_tiles = a.nseg > 1 ? (ps >= 96 ? 0 : 8) : (ps >= 112 ? 8 : 32);
+  const int64_t near_mean = T.near_pairs[src_charges][tgt_ch] / std::max<int64_t>(tgt_ch ? T.Q : T.N, 1);
+  const int fork_tiles = a.nseg > 1 ? (ps >= 96 ? 0 : 8) : ps >= 112 ? (near_mean < 700 ? 0 : 8) : 32;
   const bool m2l_first =
       f64 ? big_m2l || (a.nseg > 1 && rq.out == OUT_NGRAD && ps >= 96 && ML.n >= 2 * per_cu)
           : (combo != 0 ? ps >= 96 || nchunks > 4 * simds : ML.n >= fork_tiles * per_cu);
