@@ -29,7 +29,9 @@ class Low:
             if over < 4 * MB:
                 break
             self.blocks.append(torch.empty(over, dtype=torch.uint8, device="cuda"))
-        assert abs(torch.cuda.mem_get_info()[0] - self.left) < 16 * MB
+        # both allocators round up; the cases leave a third of the first product's memory and
+        # more on either side of what they need
+        assert abs(torch.cuda.mem_get_info()[0] - self.left) < 64 * MB
         print(f"[memory] {torch.cuda.mem_get_info()[0] / MB:.0f} MB left", flush=True)
 
     def __exit__(self, *exc):
