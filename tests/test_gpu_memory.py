@@ -29,8 +29,7 @@ class Low:
             if over < 4 * MB:
                 break
             self.blocks.append(torch.empty(over, dtype=torch.uint8, device="cuda"))
-        # both allocators round up; the cases leave a third of the first product's memory and
-        # more on either side of what they need
+        # both allocators round up; the cases have 100 MB and more to spare on either side
         assert abs(torch.cuda.mem_get_info()[0] - self.left) < 64 * MB
         print(f"[memory] {torch.cuda.mem_get_info()[0] / MB:.0f} MB left", flush=True)
 
